@@ -83,6 +83,8 @@ struct Bump {
     }
 };
 
+size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
+
 bool mul_ok(int64_t a, int64_t b, int64_t* out) {
     if (a < 0 || b < 0) return false;
     if (a != 0 && b > INT64_MAX / a) return false;
@@ -110,6 +112,23 @@ int node_scan_level(int64_t E, int D) {
         }
     }
     return level;
+}
+
+// Chunks of the vector recursions: enough workgroups to stream the edges from HBM at full rate
+// (192 of 16 waves above 128 labels, 256 of 8 above 64, 512 of 4 above 32, 1024 below), but
+// not more, and never less than kMinEdges edges: what a walk reads again is what it takes to
+// forget a guessed start, about 10 to 90 edges whatever the chunk's length.  Measured (Viterbi,
+// us per call, at least 48 / 64 / 96 / 128 edges per chunk): C = 64, B = 32, N = 512: 130 /
+// 110 / 118 / 164; C = 128, B = 4, N = 8192: 523 / 538 / 528 / 421 (256 workgroups are the
+// 128); C = 256, B = 16, N = 1024: 994 / 1006 / 959 / 1092 (192 workgroups are 86).
+void recur_chunks(int64_t B, int64_t E, int64_t C, int64_t* S, int64_t* K) {
+    constexpr int64_t kMinEdges = 64;
+    const int64_t slots = C > 128 ? 192 : C > 64 ? 256 : C > 32 ? 512 : 1024;
+    int64_t s = (B * E + slots - 1) / slots;
+    if (s < kMinEdges) s = kMinEdges;
+    const int64_t k = E / s < 1 ? 1 : E / s;
+    *S = (E + k - 1) / k;
+    *K = (E + *S - 1) / *S;
 }
 
 bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, bool masks) {
@@ -199,10 +218,12 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
                 p->v[l] = bump.take<float>(n * C);
             }
     } else {
+        const size_t area = bump.off;
         for (int l = 1; l < D; ++l) {   // the root's matrix is never formed
             const size_t n = (size_t)B * (size_t)(Np >> l);
             p->mnode[l] = bump.take<double>(n * C * C);
         }
+        const size_t area_end = bump.off;
         for (int l = 1; l < D; ++l) {
             const size_t n = (size_t)B * (size_t)(Np >> l);
             p->mu[l] = bump.take<double>(n * C);
@@ -217,7 +238,31 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
         p->dec_chunk = K;
         p->dec_nchunks = (p->E + K - 1) / K;
         p->dec_map = bump.take<uint8_t>((size_t)B * p->dec_nchunks * C);
-        p->dec_zend = bump.take<int32_t>((size_t)B * p->dec_nchunks);
+        if (!masks && !force_tree) {
+            // the recursion's scores lie in the tree's node area (the tree, if it runs at all,
+            // runs after it) when they fit there
+            recur_chunks(B, p->E, C, &p->rec_S, &p->rec_K);
+            const size_t nbk = (size_t)B * p->rec_K, versions = kRecRounds + 2;
+            auto place = [&](Bump& m) {
+                p->rec_delta = m.take<double>((size_t)B * p->E * C);
+                p->rec_vendd = m.take<double>((p->rec_K > 1 ? versions : 1) * nbk * C);
+                p->rec_chg = m.take<int32_t>(kRecRounds * nbk);
+                p->rec_shift = m.take<double>(nbk);
+                p->rec_last = m.take<int32_t>(nbk);
+            };
+            Bump probe{nullptr};
+            place(probe);
+            Bump in{bump.base ? bump.base + align_up(area) : nullptr};
+            if (align_up(area) + probe.off <= area_end) place(in);
+            else place(bump);
+            // Walks that never meet are left to one workgroup per sequence, E dependent steps;
+            // where the tree would be much faster than that (few and long sequences), it takes
+            // those sequences instead (about 29 T add/max per second, 4 us per launch)
+            const double step_us = C > 128 ? 4.0 : C > 64 ? 1.2 : C > 32 ? 0.5 : 0.35;
+            const double tree_us = 8.0 * D + 2.0 * (double)B * p->E * C * C * C / 29e6;
+            if (p->rec_K > 1 && step_us * p->E > 3 * tree_us)
+                p->gate = bump.take<int32_t>((size_t)B);
+        }
     }
     p->bytes = (bump.off + kAlign - 1) / kAlign * kAlign;
     return true;
@@ -298,8 +343,6 @@ struct Derived {
     Plan base;
     size_t extra = 0, mu = 0, part = 0, logz = 0;   // byte offsets after base.bytes
 };
-
-size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 bool plan_derived(int op, int64_t B, int64_t N, int64_t C, Derived* d) {
     const int baseOp = op == TS_OP_LOG_DENSITY ? TS_OP_LOGPARTITION : TS_OP_MARGINALS;
@@ -437,7 +480,7 @@ ts_status ts_chain_viterbi(const float* pot, const int32_t* lengths, int64_t B, 
     if (N == 1)
         return hip_status(launch_single_token(B, N, C, TS_OP_VITERBI, nullptr, path, score, s));
     if (p.fused) return hip_status(launch_small_max(pot, lengths, B, N, C, path, score, s));
-    return hip_status(launch_viterbi_tree(p, pot, lengths, path, score, s));
+    return hip_status(launch_viterbi(p, pot, lengths, path, score, s));
 }
 
 ts_status ts_chain_marginals_viterbi(const float* pot, const int32_t* lengths, int64_t B,
@@ -476,7 +519,7 @@ ts_status ts_chain_marginals_viterbi(const float* pot, const int32_t* lengths, i
     Side* side = nullptr;
     hipError_t e = side_of_current_device(&side);
     if (e == hipSuccess) e = link(side->fork, s, side->stream);
-    if (e == hipSuccess) e = launch_viterbi_tree(pv, pot, lengths, path, score, side->stream);
+    if (e == hipSuccess) e = launch_viterbi(pv, pot, lengths, path, score, side->stream);
     if (e == hipSuccess) e = launch_logz_tree(pm, pot, lengths, logZ, s);
     if (e == hipSuccess) e = launch_marginals_tree(pm, pot, lengths, marg, s);
     if (e == hipSuccess) e = link(side->join, side->stream, s);
@@ -663,7 +706,7 @@ ts_status ts_semimarkov_viterbi(const float* sp, const int32_t* lengths, int64_t
             e = launch_small_max(xp, lengths, B, N, q.KC, xs, score, s);
         } else {
             make_plan(TS_OP_VITERBI, B, N, q.KC, w + q.chain, &q.base, K > 1);
-            e = launch_viterbi_tree(q.base, xp, lengths, xs, score, s);
+            e = launch_viterbi(q.base, xp, lengths, xs, score, s);
         }
     }
     if (e == hipSuccess) e = launch_semi_decode(xs, lengths, B, N, C, path, seglen, s);

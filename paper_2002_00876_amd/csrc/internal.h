@@ -71,9 +71,20 @@ struct Plan {
     int64_t dec_chunk = 1;      // edges per decode chunk
     int64_t dec_nchunks = 0;    // chunks per sequence
     uint8_t* dec_map = nullptr; // [B, nchunks, C] label at chunk start given label at its end
-    int32_t* dec_zend = nullptr;// [B, nchunks] label at each chunk's end position
+    // chunked vector recursions (recur.h): rec_K chunks of rec_S edges per sequence (0: not
+    // taken).  With a gate, gate[b] says that sequence b is left to the tree, whose kernels
+    // then skip every other sequence.
+    int64_t rec_S = 0, rec_K = 0;
+    double* rec_delta = nullptr;   // [B, E, C] forward scores (max semiring)
+    double* rec_vendd = nullptr;   // [kRecRounds + 2][B, K, C] scores at the chunks' ends
+    int32_t* rec_chg = nullptr;    // [kRecRounds][B, K] which walks changed their end
+    double* rec_shift = nullptr;   // [B, K]
+    int32_t* rec_last = nullptr;   // [B, K]
+    int32_t* gate = nullptr;       // [B]
     size_t bytes = 0;
 };
+
+constexpr int kRecRounds = 3;  // rounds of walking a chunk again from its predecessor's end
 
 constexpr int kChunkLog = 4;   // chunks of at most 16 edges
 constexpr int kNodeScanMaxLabels = 128;   // the recursion over nodes keeps two nodes in LDS
@@ -119,7 +130,9 @@ hipError_t launch_logz_tree(const Plan& p, const float* pot, const int32_t* leng
 hipError_t launch_node_scan(const Plan& p, const int32_t* lengths, float* logZ, hipStream_t s);
 hipError_t launch_marginals_tree(const Plan& p, const float* pot, const int32_t* lengths,
                                  float* marg, hipStream_t s);
-hipError_t launch_viterbi_tree(const Plan& p, const float* pot, const int32_t* lengths,
+hipError_t launch_rec_max(const Plan& p, const float* pot, const int32_t* lengths, float* score,
+                          hipStream_t s);
+hipError_t launch_viterbi(const Plan& p, const float* pot, const int32_t* lengths,
                                int32_t* path, float* score, hipStream_t s);
 hipError_t launch_chunk_up(const Plan& p, const float* pot, const int32_t* lengths,
                            hipStream_t s);

@@ -29,6 +29,7 @@ constexpr int kMThreads = 256;
 constexpr int64_t kFewTiles = 512;   // two 128-wide tiles per compute unit
 
 struct UpMaxArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* leaves;    // level 1 reads the potentials
     const double* cnode;    // level >= 2 reads float64 nodes
     int64_t cnodes;
@@ -63,6 +64,7 @@ __global__ __launch_bounds__(kMThreads) void k_up_max_narrow(UpMaxArgs a) {
     const int tile = (int)(lid % ntiles);
     const int64_t node = lid / ntiles;
     const int64_t b = node / a.nodes, k = node % a.nodes;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t span = (int64_t)1 << a.level, half = span >> 1;
     if (k * span >= Eb) return;
@@ -185,6 +187,7 @@ __global__ __launch_bounds__((TM / 8) * (TM / 8)) void k_up_max(UpMaxArgs a) {
     const int tile = (int)(lid % ntiles);
     const int64_t node = lid / ntiles;
     const int64_t b = node / a.nodes, k = node % a.nodes;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t span = (int64_t)1 << a.level, half = span >> 1;
     if (k * span >= Eb) return;
@@ -294,6 +297,7 @@ __global__ __launch_bounds__((TM / 8) * (TM / 8)) void k_up_max(UpMaxArgs a) {
 
 // ---- forward scores down the tree: u_L = u_N, u_R = u_N (x) L
 struct DownMaxArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const double* uN;    // nullptr at the root (zeros)
     int64_t nodes;
     const double* cnode; // children (level l-1 >= 1)
@@ -308,6 +312,7 @@ template <int kS>
 __global__ __launch_bounds__(256) void k_down_max(DownMaxArgs a) {
     __shared__ double su[kMaxLabels];
     const int64_t b = blockIdx.x / a.nodes, k = blockIdx.x % a.nodes;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t C = a.C;
     const int64_t span = (int64_t)1 << a.level, half = span >> 1;
@@ -342,6 +347,7 @@ __global__ __launch_bounds__(256) void k_down_max(DownMaxArgs a) {
 
 // ---- leaves: backpointers, last label and score
 struct BpArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* pot;
     const double* u1;   // level-1 forward vectors (nullptr when level 1 is the root)
     int64_t nodes1;
@@ -398,6 +404,7 @@ __global__ __launch_bounds__(256) void k_bp_max(BpArgs a) {
     __shared__ int ri[4];
     const int64_t npairs = (a.N - 1 + 1) / 2;
     const int64_t b = blockIdx.x / npairs, k = blockIdx.x % npairs;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t C = a.C, E = a.N - 1;
     if (Eb == 0) {
@@ -450,64 +457,55 @@ __global__ __launch_bounds__(256) void k_bp_max(BpArgs a) {
 }
 
 // ---- decode
+// The backtrace in two launches: every chunk's map (the label at its start for each label at
+// its end), then every chunk's own labels, whose workgroup first follows the maps of the chunks
+// after it down from the last label.
 struct DecArgs {
     const uint8_t* bp;
     const int32_t* lengths;
     int64_t N, C, chunk, nchunks;
     uint8_t* map;       // [B, nchunks, C]
-    int32_t* zend;      // [B, nchunks]
     const int32_t* zlast;
     int32_t* path;      // [B, N]
 };
+constexpr int kDecThreads = 256;
+
+// Copies n bytes to LDS by 16-byte loads: `src` keeps its offset within 16 bytes, so the copy
+// starts at lds + (src & 15), which is returned.  The loads reach up to 15 bytes before and
+// after the n bytes, which lie in the same workspace (every buffer there starts on a 256-byte
+// boundary and the workspace ends on one).
+__device__ __forceinline__ const uint8_t* stage_bytes(uint8_t* lds, const uint8_t* src, int n) {
+    const int head = (int)((uintptr_t)src & 15);
+    const uint4* from = (const uint4*)(src - head);
+    uint4* to = (uint4*)lds;
+    for (int i = threadIdx.x; i < (head + n + 15) / 16; i += blockDim.x) to[i] = from[i];
+    return lds + head;
+}
 
 // chunk c covers edges [c*K, min((c+1)*K, E_b)); it maps the label at position
 // e_c = min((c+1)*K, E_b) to the label at position s_c = c*K, for every label at e_c.
-__global__ __launch_bounds__(256) void k_dec_map(DecArgs a) {
-    extern __shared__ uint8_t sbp[];
+__global__ __launch_bounds__(kDecThreads) void k_dec_map(DecArgs a) {
+    extern __shared__ __align__(16) uint8_t sbp[];
     const int64_t b = blockIdx.x / a.nchunks, c = blockIdx.x % a.nchunks;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1, E = a.N - 1;
     const int64_t s = c * a.chunk;
-    if (s >= Eb) return;
-    const int64_t e = min((c + 1) * a.chunk, Eb);
-    const int64_t n = (e - s) * a.C;
-    const uint8_t* src = a.bp + (size_t)(b * E + s) * a.C;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) sbp[i] = src[i];
+    if (c == 0 || s >= Eb) return;   // (nothing follows the first chunk's map)
+    const int n = (int)(min(s + a.chunk, Eb) - s), C = (int)a.C;
+    const uint8_t* m = stage_bytes(sbp, a.bp + (size_t)(b * E + s) * C, n * C);
     __syncthreads();
-    const int64_t j = threadIdx.x;
-    if (j < a.C) {
-        int z = (int)j;
-        for (int64_t t = e - 1; t >= s; --t) z = sbp[(t - s) * a.C + z];
-        a.map[(size_t)(b * a.nchunks + c) * a.C + j] = (uint8_t)z;
-    }
-}
-
-// one wave per sequence: z at every chunk end, walking the chunk maps backwards
-__global__ __launch_bounds__(64) void k_dec_walk(DecArgs a) {
-    extern __shared__ uint8_t smap[];
-    const int64_t b = blockIdx.x;
-    const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
-    if (Eb == 0) {
-        if (threadIdx.x == 0) a.zend[b * a.nchunks] = 0;
-        return;
-    }
-    const int64_t last = (Eb - 1) / a.chunk;
-    const int64_t n = (last + 1) * a.C;
-    const uint8_t* src = a.map + (size_t)b * a.nchunks * a.C;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) smap[i] = src[i];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int z = a.zlast[b];
-        for (int64_t c = last; c >= 0; --c) {
-            a.zend[b * a.nchunks + c] = z;
-            z = smap[c * a.C + z];
-        }
+    const int j = threadIdx.x;
+    if (j < C) {
+        int z = j;
+        for (int t = n - 1; t >= 0; --t) z = m[t * C + z];
+        a.map[(size_t)(b * a.nchunks + c) * C + j] = (uint8_t)z;
     }
 }
 
 // each chunk writes the labels of positions (s_c, e_c] (chunk 0 also position 0) and -1
 // for its positions at or past the length
-__global__ __launch_bounds__(64) void k_dec_emit(DecArgs a) {
-    extern __shared__ uint8_t sbp[];
+__global__ __launch_bounds__(kDecThreads) void k_dec_emit(DecArgs a) {
+    extern __shared__ __align__(16) uint8_t sbuf[];
+    __shared__ int zend;
     const int64_t b = blockIdx.x / a.nchunks, c = blockIdx.x % a.nchunks;
     const int64_t L = clamp_len(a.lengths, b, a.N), Eb = L - 1, E = a.N - 1;
     const int64_t s = c * a.chunk;
@@ -516,30 +514,41 @@ __global__ __launch_bounds__(64) void k_dec_emit(DecArgs a) {
     for (int64_t n = s + 1 + threadIdx.x; n <= min(s + a.chunk, E); n += blockDim.x)
         if (n >= L) path[n] = -1;
     if (Eb == 0) {
-        if (c == 0 && threadIdx.x == 0) path[0] = a.zend[b * a.nchunks];
+        if (c == 0 && threadIdx.x == 0) path[0] = a.zlast[b];
         return;
     }
     if (s >= Eb) return;
-    const int64_t e = min((c + 1) * a.chunk, Eb);
-    const int64_t n = (e - s) * a.C;
-    const uint8_t* src = a.bp + (size_t)(b * E + s) * a.C;
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) sbp[i] = src[i];
+    const int C = (int)a.C;
+    // the label at this chunk's end, through the maps of chunks last .. c + 1
+    const int later = (int)((Eb - 1) / a.chunk - c);
+    const uint8_t* m = stage_bytes(sbuf, a.map + (size_t)(b * a.nchunks + c + 1) * C, later * C);
     __syncthreads();
     if (threadIdx.x == 0) {
-        int z = a.zend[b * a.nchunks + c];
-        path[e] = z;
-        for (int64_t t = e - 1; t >= s; --t) {
-            z = sbp[(t - s) * a.C + z];
-            if (t > s || c == 0) path[t] = z;
+        int z = a.zlast[b];
+        for (int i = later - 1; i >= 0; --i) z = m[i * C + z];
+        zend = z;
+    }
+    __syncthreads();
+    const int n = (int)(min(s + a.chunk, Eb) - s);
+    m = stage_bytes(sbuf, a.bp + (size_t)(b * E + s) * C, n * C);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int z = zend;
+        path[s + n] = z;
+        for (int t = n - 1; t >= 0; --t) {
+            z = m[t * C + z];
+            if (t > 0 || c == 0) path[s + t] = z;
         }
     }
 }
 
-
 }  // namespace
 
-hipError_t launch_viterbi_tree(const Plan& p, const float* pot, const int32_t* lengths,
-                               int32_t* path, float* score, hipStream_t s) {
+namespace {
+
+// Backpointers, last labels and scores by the tree (of the sequences that p.gate marks)
+hipError_t launch_tree(const Plan& p, const float* pot, const int32_t* lengths, float* score,
+                       hipStream_t s) {
     const int64_t C = p.C;
     // levels below the root: the forward scores start from the root with zeros and only
     // read its children's matrices
@@ -552,6 +561,7 @@ hipError_t launch_viterbi_tree(const Plan& p, const float* pot, const int32_t* l
         const int tmax = narrow ? kMT : 2 * kMT;
         const int ntm = (int)((C + tmax - 1) / tmax);
         UpMaxArgs a{};
+        a.gate = p.gate;
         a.leaves = (l == 1) ? pot : nullptr;
         a.cnode = (l == 1) ? nullptr : p.mnode[l - 1];
         a.cnodes = (l == 1) ? p.E : (p.Np >> (l - 1));
@@ -573,6 +583,7 @@ hipError_t launch_viterbi_tree(const Plan& p, const float* pot, const int32_t* l
     }
     for (int l = p.D; l >= 2; --l) {
         DownMaxArgs d{};
+        d.gate = p.gate;
         d.uN = (l == p.D) ? nullptr : p.mu[l];
         d.nodes = p.Np >> l;
         d.cnode = p.mnode[l - 1];
@@ -587,6 +598,7 @@ hipError_t launch_viterbi_tree(const Plan& p, const float* pot, const int32_t* l
         if (e != hipSuccess) return e;
     }
     BpArgs bpa{};
+    bpa.gate = p.gate;
     bpa.pot = pot;
     bpa.u1 = (p.D >= 2) ? p.mu[1] : nullptr;
     bpa.nodes1 = (p.D >= 1) ? (p.Np >> 1) : 1;
@@ -598,21 +610,42 @@ hipError_t launch_viterbi_tree(const Plan& p, const float* pot, const int32_t* l
     if (C <= 64) hipLaunchKernelGGL(k_bp_max<4>, bgrid, dim3(256), 0, s, bpa);
     else if (C <= 128) hipLaunchKernelGGL(k_bp_max<2>, bgrid, dim3(256), 0, s, bpa);
     else hipLaunchKernelGGL(k_bp_max<1>, bgrid, dim3(256), 0, s, bpa);
-    hipError_t e = hipGetLastError();
+    return hipGetLastError();
+}
+
+// The decode kernels' tables take up to 64 KiB of LDS and the ends of two 16-byte loads
+hipError_t allow_decode_lds() {
+    static const hipError_t attr = [] {
+        const auto kAttr = hipFuncAttributeMaxDynamicSharedMemorySize;
+        const hipError_t e = hipFuncSetAttribute((const void*)k_dec_map, kAttr, 65536 + 32);
+        return e == hipSuccess ? hipFuncSetAttribute((const void*)k_dec_emit, kAttr, 65536 + 32) : e;
+    }();
+    return attr;
+}
+
+}  // namespace
+
+hipError_t launch_viterbi(const Plan& p, const float* pot, const int32_t* lengths,
+                          int32_t* path, float* score, hipStream_t s) {
+    const int64_t C = p.C;
+    hipError_t e = hipSuccess;
+    if (p.rec_K > 0) e = launch_rec_max(p, pot, lengths, score, s);
+    if (e == hipSuccess && (p.rec_K == 0 || p.gate)) e = launch_tree(p, pot, lengths, score, s);
     if (e != hipSuccess) return e;
 
     DecArgs d{};
     d.bp = p.bp; d.lengths = lengths; d.N = p.N; d.C = C; d.chunk = p.dec_chunk;
-    d.nchunks = p.dec_nchunks; d.map = p.dec_map; d.zend = p.dec_zend; d.zlast = p.zlast;
-    d.path = path;
-    const size_t chunk_bytes = (size_t)p.dec_chunk * C;
-    hipLaunchKernelGGL(k_dec_map, dim3((unsigned)(p.B * p.dec_nchunks)), dim3(256), chunk_bytes,
-                       s, d);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dec_walk, dim3((unsigned)p.B), dim3(64), (size_t)p.dec_nchunks * C, s, d);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dec_emit, dim3((unsigned)(p.B * p.dec_nchunks)), dim3(64), chunk_bytes,
-                       s, d);
+    d.nchunks = p.dec_nchunks; d.map = p.dec_map; d.zlast = p.zlast; d.path = path;
+    // each at most 64 KiB (make_plan), and the bytes around it that stage_bytes copies
+    const size_t chunk_bytes = (size_t)std::min(p.dec_chunk, p.E) * C + 32;
+    const size_t emit_bytes = std::max(chunk_bytes, (size_t)(p.dec_nchunks - 1) * C + 32);
+    if ((e = allow_decode_lds()) != hipSuccess) return e;
+    const dim3 grid((unsigned)(p.B * p.dec_nchunks));
+    if (p.dec_nchunks > 1) {
+        hipLaunchKernelGGL(k_dec_map, grid, dim3(kDecThreads), chunk_bytes, s, d);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_dec_emit, grid, dim3(kDecThreads), emit_bytes, s, d);
     return hipGetLastError();
 }
 

@@ -1,0 +1,74 @@
+"""Parity of the chunked vector recursions (several chunks per sequence) with the float64
+oracle: every lane layout at its edge label counts, chains that forget their start quickly,
+slowly, or never (the sequences that the tree has to compute), ties, -inf structure and
+ragged lengths."""
+import numpy as np
+import pytest
+
+from gpu_util import check_all
+from paper_2002_00876_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# every layout: rows of 16-byte loads (C a multiple of 4) and of single entries, at the largest
+# and smallest label counts of each
+LABELS = [2, 7, 20, 31, 32, 33, 36, 63, 64, 65, 68, 95, 96, 97, 100, 127, 128, 129, 132, 191, 192,
+          193, 196, 255, 256]
+
+
+@pytest.mark.parametrize("C", LABELS)
+def test_layouts(C):
+    N = 390 if C > 32 else 700
+    pot, lens = W.random_case(31000 + C, 4, N, C, sigma=1.0,
+                              lengths=[N, N - 1, N // 2 + 1, 2])
+    check_all(pot, lens, f"layout C={C}")
+
+
+@pytest.mark.parametrize("C", [36, 50, 100, 101, 200])
+def test_integer_ties(C):
+    pot, lens = W.random_case(32000 + C, 3, 400, C, kind="int", int_range=1,
+                              lengths=[400, 257, 130])
+    check_all(pot, lens, f"ties C={C}")
+
+
+def _sticky(seed, B, N, C, stay):
+    # labels keep themselves with a bonus: the chain remembers its start for long
+    rng = np.random.default_rng(seed)
+    pot = rng.standard_normal((B, N - 1, C, C)).astype(np.float32)
+    pot += np.float32(stay) * np.eye(C, dtype=np.float32)
+    return pot, np.array([N, N - 70, 1][:B], np.int32)
+
+
+@pytest.mark.parametrize("C,stay", [(40, 6.0), (40, 12.0), (101, 8.0), (128, 14.0), (200, 9.0)])
+def test_slow_mixing(C, stay):
+    pot, lens = _sticky(33000 + C, 3, 500, C, stay)
+    check_all(pot, lens, f"sticky C={C} stay={stay}")
+
+
+@pytest.mark.parametrize("C", [40, 70, 128])
+def test_never_mixing(C):
+    # two label sets without transitions between them: the walks never agree
+    rng = np.random.default_rng(34000 + C)
+    pot = rng.standard_normal((3, 330, C, C)).astype(np.float32)
+    pot[1:, :, :C // 2, C // 2:] = -np.inf
+    pot[1:, :, C // 2:, :C // 2] = -np.inf
+    check_all(pot, np.array([331, 331, 200], np.int32), f"two components C={C}")
+
+
+@pytest.mark.parametrize("C", [48, 65, 256])
+def test_left_to_right_structure(C):
+    # label i reaches labels i .. i + 3 only
+    rng = np.random.default_rng(35000 + C)
+    pot = rng.standard_normal((2, 300, C, C)).astype(np.float32)
+    i, j = np.indices((C, C))
+    pot[:, :, (j < i) | (j > i + 3)] = -np.inf
+    check_all(pot, np.array([301, 150], np.int32), f"left to right C={C}")
+
+
+@pytest.mark.parametrize("C", [36, 129])
+def test_no_finite_path_in_a_later_chunk(C):
+    rng = np.random.default_rng(36000 + C)
+    pot = rng.standard_normal((3, 400, C, C)).astype(np.float32)
+    pot[1, 190] = -np.inf                       # sequence 1 is cut in two
+    pot[2, 250, :, 1:] = -np.inf                # sequence 2 passes through label 0
+    check_all(pot, np.array([401, 401, 401], np.int32), f"cut C={C}")
