@@ -131,6 +131,9 @@ void recur_chunks(int64_t B, int64_t E, int64_t C, int64_t* S, int64_t* K) {
     *K = (E + *S - 1) / *S;
 }
 
+// About what one step of one workgroup's walk takes, without other work on its compute unit
+double walk_step_us(int64_t C) { return C > 128 ? 4.0 : C > 64 ? 1.2 : C > 32 ? 0.5 : 0.35; }
+
 bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, bool masks) {
     *p = Plan{};
     p->B = B; p->N = N; p->C = C; p->E = N - 1; p->op = op;
@@ -156,6 +159,40 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
     while (Np < p->E) { Np <<= 1; ++D; }
     p->Np = Np; p->D = D;
     Bump bump{static_cast<char*>(base)};
+    // The vector recursions' buffers lie in the first buffers of the tree or chunk path [0, used)
+    // when they fit there (those kernels, if they run at all, run after the recursions); the
+    // gate, which outlives them, is a buffer of its own.
+    const bool recur = !force_tree;
+    if (recur) recur_chunks(B, p->E, C, &p->rec_S, &p->rec_K);
+    const size_t nbk = (size_t)B * p->rec_K, versions = p->rec_K > 1 ? kRecRounds + 2 : 1;
+    auto place_recur = [&](size_t used, auto&& place) {
+        Bump probe{nullptr};
+        place(probe);
+        Bump in{bump.base};
+        if (probe.off <= used) place(in);
+        else place(bump);
+    };
+    auto place_log = [&](size_t used, double chain_us) {
+        place_recur(used, [&](Bump& m) {
+            const size_t n = (size_t)B * p->E;
+            p->rec_alpha = m.take<float>(n * C);
+            p->rec_cx = m.take<int32_t>(n);
+            p->rec_vend = m.take<float>(versions * nbk * C);
+            p->rec_xend = m.take<int32_t>(versions * nbk);
+            p->rec_chg = m.take<int32_t>((kRecRounds + 1) * nbk);
+            p->rec_shift = m.take<double>(nbk);
+            p->rec_last = m.take<int32_t>(nbk);
+            p->rec_bad = m.take<int32_t>(nbk);
+            if (op != TS_OP_MARGINALS) return;
+            p->rec_beta = m.take<float>(n * C);
+            p->rec_vbeg = m.take<float>(versions * nbk * C);
+            p->rec_chgb = m.take<int32_t>((kRecRounds + 1) * nbk);
+            p->rec_badb = m.take<int32_t>(nbk);
+            p->rec_gateb = m.take<int32_t>((size_t)B);
+        });
+        p->gate = bump.take<int32_t>((size_t)B);
+        p->rec_tree = (op == TS_OP_MARGINALS ? 2 : 1) * walk_step_us(C) * p->E > chain_us;
+    };
     if (op == TS_OP_LOGPARTITION || op == TS_OP_MARGINALS) {
         p->chunk = chunk_path(C, masks);
         if (p->chunk) {
@@ -186,6 +223,8 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
                 p->u[lc] = bump.take<float>(nv * C);
                 p->v[lc] = bump.take<float>(nv * C);
             }
+            // (the chunk kernels sustain about 40 TFLOP/s of products)
+            if (recur) place_log(bump.off, 30.0 + 2.0 * (double)B * p->E * C * C * C / 40e6);
             p->bytes = (bump.off + kAlign - 1) / kAlign * kAlign;
             return true;
         }
@@ -217,13 +256,14 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
                 p->u[l] = bump.take<float>(n * C);
                 p->v[l] = bump.take<float>(n * C);
             }
+        // (as does the tree, at 8 us per level and sweep)
+        if (recur) place_log(bump.off, 16.0 * D + 2.0 * (double)B * p->E * C * C * C / 40e6);
     } else {
-        const size_t area = bump.off;
         for (int l = 1; l < D; ++l) {   // the root's matrix is never formed
             const size_t n = (size_t)B * (size_t)(Np >> l);
             p->mnode[l] = bump.take<double>(n * C * C);
         }
-        const size_t area_end = bump.off;
+        const size_t used = bump.off;
         for (int l = 1; l < D; ++l) {
             const size_t n = (size_t)B * (size_t)(Np >> l);
             p->mu[l] = bump.take<double>(n * C);
@@ -238,29 +278,19 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
         p->dec_chunk = K;
         p->dec_nchunks = (p->E + K - 1) / K;
         p->dec_map = bump.take<uint8_t>((size_t)B * p->dec_nchunks * C);
-        if (!masks && !force_tree) {
-            // the recursion's scores lie in the tree's node area (the tree, if it runs at all,
-            // runs after it) when they fit there
-            recur_chunks(B, p->E, C, &p->rec_S, &p->rec_K);
-            const size_t nbk = (size_t)B * p->rec_K, versions = kRecRounds + 2;
-            auto place = [&](Bump& m) {
+        if (recur) {
+            place_recur(used, [&](Bump& m) {
                 p->rec_delta = m.take<double>((size_t)B * p->E * C);
-                p->rec_vendd = m.take<double>((p->rec_K > 1 ? versions : 1) * nbk * C);
+                p->rec_vendd = m.take<double>(versions * nbk * C);
                 p->rec_chg = m.take<int32_t>(kRecRounds * nbk);
                 p->rec_shift = m.take<double>(nbk);
                 p->rec_last = m.take<int32_t>(nbk);
-            };
-            Bump probe{nullptr};
-            place(probe);
-            Bump in{bump.base ? bump.base + align_up(area) : nullptr};
-            if (align_up(area) + probe.off <= area_end) place(in);
-            else place(bump);
+            });
             // Walks that never meet are left to one workgroup per sequence, E dependent steps;
             // where the tree would be much faster than that (few and long sequences), it takes
             // those sequences instead (about 29 T add/max per second, 4 us per launch)
-            const double step_us = C > 128 ? 4.0 : C > 64 ? 1.2 : C > 32 ? 0.5 : 0.35;
             const double tree_us = 8.0 * D + 2.0 * (double)B * p->E * C * C * C / 29e6;
-            if (p->rec_K > 1 && step_us * p->E > 3 * tree_us)
+            if (p->rec_K > 1 && walk_step_us(C) * p->E > 3 * tree_us)
                 p->gate = bump.take<int32_t>((size_t)B);
         }
     }
@@ -359,6 +389,16 @@ bool plan_derived(int op, int64_t B, int64_t N, int64_t C, Derived* d) {
     return true;
 }
 
+// log Z (unless nullptr) and the marginals (unless nullptr) of a plan with a workspace
+hipError_t log_call(const Plan& p, const float* pot, const int32_t* lengths, float* logZ,
+                    float* marg, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    if (p.rec_K > 0) e = launch_rec_log(p, pot, lengths, logZ, marg, s);
+    // what the recursions leave (p.gate), or everything
+    if (e == hipSuccess) e = launch_logz_tree(p, pot, lengths, logZ, s);
+    return e == hipSuccess && marg ? launch_marginals_tree(p, pot, lengths, marg, s) : e;
+}
+
 ts_status hip_status(hipError_t e) {
     if (e == hipSuccess) return TS_OK;
     return fail(TS_ERR_HIP, std::string("HIP error: ") + hipGetErrorString(e));
@@ -444,7 +484,7 @@ ts_status ts_chain_logpartition(const float* pot, const int32_t* lengths, int64_
     if (N == 1) return hip_status(launch_single_token(B, N, C, TS_OP_LOGPARTITION, logZ,
                                                       nullptr, nullptr, s));
     if (p.fused) return hip_status(launch_small_log(pot, lengths, B, N, C, logZ, nullptr, s));
-    return hip_status(launch_logz_tree(p, pot, lengths, logZ, s));
+    return hip_status(log_call(p, pot, lengths, logZ, nullptr, s));
 }
 
 ts_status ts_chain_marginals(const float* pot, const int32_t* lengths, int64_t B, int64_t N,
@@ -462,10 +502,7 @@ ts_status ts_chain_marginals(const float* pot, const int32_t* lengths, int64_t B
                                               nullptr, s));
     }
     if (p.fused) return hip_status(launch_small_log(pot, lengths, B, N, C, logZ, marg, s));
-    // up-sweep (and log Z when requested), then the outside sweep and the marginals
-    hipError_t e = launch_logz_tree(p, pot, lengths, logZ, s);
-    if (e != hipSuccess) return hip_status(e);
-    return hip_status(launch_marginals_tree(p, pot, lengths, marg, s));
+    return hip_status(log_call(p, pot, lengths, logZ, marg, s));
 }
 
 ts_status ts_chain_viterbi(const float* pot, const int32_t* lengths, int64_t B, int64_t N,
@@ -520,8 +557,7 @@ ts_status ts_chain_marginals_viterbi(const float* pot, const int32_t* lengths, i
     hipError_t e = side_of_current_device(&side);
     if (e == hipSuccess) e = link(side->fork, s, side->stream);
     if (e == hipSuccess) e = launch_viterbi(pv, pot, lengths, path, score, side->stream);
-    if (e == hipSuccess) e = launch_logz_tree(pm, pot, lengths, logZ, s);
-    if (e == hipSuccess) e = launch_marginals_tree(pm, pot, lengths, marg, s);
+    if (e == hipSuccess) e = log_call(pm, pot, lengths, logZ, marg, s);
     if (e == hipSuccess) e = link(side->join, side->stream, s);
     return hip_status(e);
 }
@@ -545,8 +581,7 @@ ts_status ts_chain_entropy(const float* pot, const int32_t* lengths, int64_t B, 
         e = launch_small_log(pot, lengths, B, N, C, nullptr, mu, s);
     } else {
         make_plan(TS_OP_MARGINALS, B, N, C, ws, &d.base);
-        e = launch_logz_tree(d.base, pot, lengths, nullptr, s);
-        if (e == hipSuccess) e = launch_marginals_tree(d.base, pot, lengths, mu, s);
+        e = log_call(d.base, pot, lengths, nullptr, mu, s);
     }
     if (e == hipSuccess) e = launch_entropy(mu, lengths, B, N, C, part, entropy, s);
     return hip_status(e);
@@ -572,7 +607,7 @@ ts_status ts_chain_log_density(const float* pot, const int32_t* lengths, const i
         e = launch_small_log(pot, lengths, B, N, C, logz, nullptr, s);
     } else {
         make_plan(TS_OP_LOGPARTITION, B, N, C, ws, &d.base);
-        e = launch_logz_tree(d.base, pot, lengths, logz, s);
+        e = log_call(d.base, pot, lengths, logz, nullptr, s);
     }
     if (e == hipSuccess) e = launch_log_density(pot, lengths, labels, logz, B, N, C, logp, s);
     return hip_status(e);
@@ -602,8 +637,7 @@ ts_status ts_chain_sample(const float* pot, const int32_t* lengths, const float*
             e = launch_small_log(pot, lengths, B, N, C, nullptr, mu, s);
         } else {
             make_plan(TS_OP_MARGINALS, B, N, C, ws, &d.base);
-            e = launch_logz_tree(d.base, pot, lengths, nullptr, s);
-            if (e == hipSuccess) e = launch_marginals_tree(d.base, pot, lengths, mu, s);
+            e = log_call(d.base, pot, lengths, nullptr, mu, s);
         }
     }
     if (e == hipSuccess) e = launch_sample(mu, lengths, uniforms, S, B, N, C, paths, s);
@@ -646,7 +680,7 @@ ts_status ts_semimarkov_logpartition(const float* sp, const int32_t* lengths, in
             e = launch_small_log(xp, lengths, B, N, q.KC, logZ, nullptr, s);
         } else {
             make_plan(TS_OP_LOGPARTITION, B, N, q.KC, w + q.chain, &q.base, K > 1);
-            e = launch_logz_tree(q.base, xp, lengths, logZ, s);
+            e = log_call(q.base, xp, lengths, logZ, nullptr, s);
         }
     }
     if (e == hipSuccess) e = launch_semi_single(lengths, B, N, C, logZ, s);
@@ -676,8 +710,7 @@ ts_status ts_semimarkov_marginals(const float* sp, const int32_t* lengths, int64
             e = launch_small_log(xp, lengths, B, N, q.KC, logZ, xm, s);
         } else {
             make_plan(TS_OP_MARGINALS, B, N, q.KC, w + q.chain, &q.base, K > 1);
-            e = launch_logz_tree(q.base, xp, lengths, logZ, s);
-            if (e == hipSuccess) e = launch_marginals_tree(q.base, xp, lengths, xm, s);
+            e = log_call(q.base, xp, lengths, logZ, xm, s);
         }
     }
     if (e == hipSuccess) e = launch_semi_gather(xm, B, N, K, C, marg, s);

@@ -86,6 +86,7 @@ __device__ __forceinline__ float wave_lse64(float x) {
 }
 
 struct ChunkUpArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* pot;
     const int32_t* lengths;
     int64_t N, C;
@@ -568,6 +569,7 @@ __global__ __launch_bounds__(kCT, 4) void k_chunk_up(ChunkUpArgs a) {
     __shared__ ChunkUpSmem sm;
     __shared__ int flag[2];
     const int64_t b = blockIdx.x / a.nodes, q = blockIdx.x % a.nodes;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t S = (int64_t)1 << a.lc, t0 = q * S;
     if (t0 >= Eb) return;   // node absent: all padding
@@ -580,6 +582,7 @@ __global__ __launch_bounds__(kCT, 4) void k_chunk_up(ChunkUpArgs a) {
 }
 
 struct ChunkFormArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* pot;
     const int32_t* lengths;
     int64_t N, C;
@@ -634,6 +637,7 @@ __global__ __launch_bounds__(kCT) void k_chunk_form(ChunkFormArgs a) {
     __shared__ float hs[kMaxChunk];                          // h_t: the shift of alpha_{t+1}
     __shared__ __align__(16) float pm[2][4][kCP], ps[2][4][kCP];   // partial states, ping-pong
     const int64_t b = blockIdx.x / a.nodes, q = blockIdx.x % a.nodes;
+    if (a.gate && !a.gate[b]) return;
     const int64_t E = a.N - 1, Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t S = (int64_t)1 << a.lc, t0 = q * S;
     const int64_t tall = min(t0 + S, E);
@@ -798,6 +802,7 @@ __global__ __launch_bounds__(kCT) void k_chunk_form(ChunkFormArgs a) {
 // stored as float; the shifts are summed in float64 for log Z.  The matrices are independent of the vectors, so
 // they are loaded kScanAhead steps ahead of their use and each step costs one barrier.
 struct ChunkScanArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* core;    // [B * nodes][C][C]: the chunk nodes, or the potentials when lc == 0
     const double* ro;     // [B * nodes][C] (nullptr: zeros, lc == 0)
     const double* co;
@@ -819,6 +824,7 @@ __global__ __launch_bounds__(kCT) void k_chunk_scan(ChunkScanArgs a) {
     const bool fwd = blockIdx.x < gridDim.x / (a.v ? 2 : 1) || !a.v;
     const int64_t B = a.v ? gridDim.x / 2 : gridDim.x;
     const int64_t b = fwd ? blockIdx.x : blockIdx.x - B;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int C = (int)a.C, tid = threadIdx.x, lane = tid & (kWave - 1), w = tid >> 6;
     const int rg = tid >> 4, c4 = tid & 15;
@@ -1000,6 +1006,7 @@ bool chunk_path(int64_t C, bool masks) { return !masks && C <= kCP; }
 hipError_t launch_chunk_up(const Plan& p, const float* pot, const int32_t* lengths,
                            hipStream_t s) {
     ChunkUpArgs a{};
+    a.gate = p.gate;
     a.pot = pot; a.lengths = lengths; a.N = p.N; a.C = p.C;
     a.lc = p.lc;
     a.nodes = p.Np >> p.lc;
@@ -1017,6 +1024,7 @@ hipError_t launch_chunk_up(const Plan& p, const float* pot, const int32_t* lengt
 hipError_t launch_chunk_scan(const Plan& p, const float* pot, const int32_t* lengths,
                              float* logZ, hipStream_t s) {
     ChunkScanArgs a{};
+    a.gate = p.gate;
     if (p.lc > 0) {
         a.core = p.core[p.lc]; a.ro = p.ro[p.lc]; a.co = p.co[p.lc]; a.lin = p.clin;
         a.nodes = p.Np >> p.lc;
@@ -1038,6 +1046,7 @@ hipError_t launch_chunk_scan(const Plan& p, const float* pot, const int32_t* len
 hipError_t launch_chunk_form(const Plan& p, const float* pot, const int32_t* lengths,
                              float* marg, hipStream_t s) {
     ChunkFormArgs a{};
+    a.gate = p.gate;
     a.pot = pot; a.lengths = lengths; a.N = p.N; a.C = p.C;
     a.lc = p.lc;
     a.nodes = p.Np >> p.lc;

@@ -57,6 +57,12 @@ __device__ __forceinline__ void buffer_store4(float4 v, __amdgpu_buffer_rsrc_t r
     typedef int v4i __attribute__((ext_vector_type(4)));
     const v4i x = {__float_as_int(v.x), __float_as_int(v.y), __float_as_int(v.z), __float_as_int(v.w)};
     __builtin_amdgcn_raw_buffer_store_b128(x, r, voff, soff, 0);
+    // A vector instruction that overwrites the data of a store of more than 64 bits needs two
+    // wait states after it.  The compiler leaves them out when the offset is in a scalar
+    // register, but gfx950 needs them there, too: without them single dwords of lanes 12 to 15
+    // of each 16 were stored as what the next instruction had written.  The data are operands
+    // of the wait, so that their registers are not reused before it.
+    asm volatile("s_nop 1" ::"v"(x) : "memory");
 }
 __device__ __forceinline__ float buffer_load1(__amdgpu_buffer_rsrc_t r, unsigned voff, int soff) {
     return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));

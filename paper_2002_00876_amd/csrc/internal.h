@@ -77,14 +77,27 @@ struct Plan {
     int64_t rec_S = 0, rec_K = 0;
     double* rec_delta = nullptr;   // [B, E, C] forward scores (max semiring)
     double* rec_vendd = nullptr;   // [kRecRounds + 2][B, K, C] scores at the chunks' ends
-    int32_t* rec_chg = nullptr;    // [kRecRounds][B, K] which walks changed their end
+    int32_t* rec_chg = nullptr;    // [kRecRounds (+ 1 in the log semiring)][B, K] which walks
+                                   // changed their end
     double* rec_shift = nullptr;   // [B, K]
     int32_t* rec_last = nullptr;   // [B, K]
+    // log semiring: vectors and exponents of the forward walks, vectors of the backward ones
+    float* rec_alpha = nullptr;    // [B, E, C]
+    int32_t* rec_cx = nullptr;     // [B, E]
+    float* rec_vend = nullptr;     // [kRecRounds + 2][B, K, C]
+    int32_t* rec_xend = nullptr;   // [kRecRounds + 2][B, K]
+    int32_t* rec_bad = nullptr;    // [B, K] the chunk has left the walks' range
+    float* rec_beta = nullptr;     // [B, E, C]
+    float* rec_vbeg = nullptr;     // [kRecRounds + 2][B, K, C]
+    int32_t* rec_chgb = nullptr;   // [kRecRounds + 1][B, K]
+    int32_t* rec_badb = nullptr;   // [B, K]
+    int32_t* rec_gateb = nullptr;  // [B]
+    bool rec_tree = false;         // walks that do not meet are left to the tree
     int32_t* gate = nullptr;       // [B]
     size_t bytes = 0;
 };
 
-constexpr int kRecRounds = 3;  // rounds of walking a chunk again from its predecessor's end
+constexpr int kRecRounds = 2;  // rounds of walking a chunk again from its predecessor's end
 
 constexpr int kChunkLog = 4;   // chunks of at most 16 edges
 constexpr int kNodeScanMaxLabels = 128;   // the recursion over nodes keeps two nodes in LDS
@@ -130,6 +143,8 @@ hipError_t launch_logz_tree(const Plan& p, const float* pot, const int32_t* leng
 hipError_t launch_node_scan(const Plan& p, const int32_t* lengths, float* logZ, hipStream_t s);
 hipError_t launch_marginals_tree(const Plan& p, const float* pot, const int32_t* lengths,
                                  float* marg, hipStream_t s);
+hipError_t launch_rec_log(const Plan& p, const float* pot, const int32_t* lengths, float* logZ,
+                          float* marg, hipStream_t s);
 hipError_t launch_rec_max(const Plan& p, const float* pot, const int32_t* lengths, float* score,
                           hipStream_t s);
 hipError_t launch_viterbi(const Plan& p, const float* pot, const int32_t* lengths,

@@ -26,6 +26,7 @@ constexpr int kNsParts = kNsThreads / kNodeScanMaxLabels;   // threads per colum
 constexpr int kNsRegs = kNodeScanMaxLabels * kNodeScanMaxLabels / kNsThreads;   // node values per thread
 
 struct NodeScanArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* core;     // [B * nodes][C][C] level-l nodes
     const double* ro;      // [B * nodes][C]
     const double* co;
@@ -45,6 +46,7 @@ __global__ __launch_bounds__(kNsThreads) void k_node_scan_log(NodeScanArgs a) {
     __shared__ float red[2][kNsThreads / kWave];
     __shared__ float sred[kNsThreads / kWave];
     const int64_t b = blockIdx.x;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int C = (int)a.C, CC = C * C, tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
     if (Eb <= 0) {
@@ -216,7 +218,7 @@ hipError_t allow_ns_lds() {
 
 hipError_t launch_node_scan(const Plan& p, const int32_t* lengths, float* logZ, hipStream_t s) {
     const int l = p.scan_level;
-    NodeScanArgs a{p.core[l], p.ro[l], p.co[l], p.Np >> l, lengths, p.N, p.C, l, logZ};
+    NodeScanArgs a{p.gate, p.core[l], p.ro[l], p.co[l], p.Np >> l, lengths, p.N, p.C, l, logZ};
     const size_t lds = 2 * sizeof(float) * p.C * p.C;
     hipError_t e;
     if (p.C % 4 == 0) {

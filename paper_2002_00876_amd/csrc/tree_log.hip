@@ -46,6 +46,7 @@ __device__ __forceinline__ size_t mat_off(int64_t b, int64_t k, int64_t nodes, i
 // (16-byte loads along it) and one thread per column over all rows.  Column loads are
 // coalesced across threads.
 struct LeafMaxArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* pot;
     const int32_t* lengths;
     int64_t N, C;
@@ -77,6 +78,7 @@ template <bool kVec, bool kBits>
 __global__ __launch_bounds__(256) void k_leaf_max(LeafMaxArgs a) {
     const int64_t E = a.N - 1;
     const int64_t b = blockIdx.x / E, t = blockIdx.x % E;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     if (t >= Eb) return;
     const bool left = (t & 1) == 0, right = (t & 1) == 1 || t + 1 == Eb;
@@ -196,6 +198,7 @@ __global__ __launch_bounds__(kLeafLdsThreads) void k_leaf_max_lds(LeafMaxArgs a)
     extern __shared__ float T[];   // [C][C + 1]
     const int64_t E = a.N - 1;
     const int64_t b = blockIdx.x / E, t = blockIdx.x % E;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     if (t >= Eb) return;
     const bool left = (t & 1) == 0, right = (t & 1) == 1 || t + 1 == Eb;
@@ -277,6 +280,7 @@ __global__ __launch_bounds__(kLeafLdsThreads) void k_leaf_max_lds(LeafMaxArgs a)
 // only has to bound its line from above (nothing overflows) and be close to its maximum;
 // S < 2^-80 (every term underflowed) is recomputed exactly by a direct log-sum-exp.
 struct UpLogArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* ccore;   // children (level l-1) core, or the potentials when l == 1
     const double* cro;    // nullptr when l == 1 (leaves have ro = co = 0)
     const double* cco;
@@ -349,6 +353,7 @@ __global__ __launch_bounds__(kUpThreads) void k_up_log(UpLogArgs a) {
     const int tile = (int)(lid % ntiles);
     const int64_t node = lid / ntiles;
     const int64_t b = node / a.nodes, k = node % a.nodes;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t span = (int64_t)1 << a.level, half = span >> 1;
     if (k * span >= Eb) return;  // node absent: all padding
@@ -796,6 +801,7 @@ __global__ __launch_bounds__(kUpThreads) void k_up_log_small(UpLogArgs a) {
             if (q < cnt) pm = fmaxf(pm, pp[q]);
     }
 
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t span = (int64_t)1 << a.level, half = span >> 1;
     if (k * span >= Eb) return;   // node absent: all padding
@@ -1053,6 +1059,7 @@ void k_up_log_full(UpLogArgs a) {
     const int tile = (int)(lid % ntiles);
     const int64_t node = lid / ntiles;
     const int64_t b = node / a.nodes, k = node % a.nodes;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t span = (int64_t)1 << a.level, half = span >> 1;
     if (k * span >= Eb) return;  // node absent: all padding
@@ -1609,6 +1616,7 @@ void k_up_log_full(UpLogArgs a) {
 
 // ---------------------------------------------------------------- root: log Z
 struct RootArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* core;   // level D core, or the potentials when D == 0
     const double* ro;    // nullptr when D == 0
     const double* co;
@@ -1628,6 +1636,7 @@ __global__ __launch_bounds__(kRootThreads) void k_root_log(RootArgs a) {
     __shared__ double redd[2 * kRootThreads / kWave];
     __shared__ float rof[kMaxLabels], cof[kMaxLabels];   // offsets less their maxima
     const int64_t b = blockIdx.x;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int C = (int)a.C, CC = C * C, tid = threadIdx.x;
     if (Eb == 0) {
@@ -1905,6 +1914,7 @@ __device__ void half_vec(bool active, const float* core, const double* ro, const
 }
 
 struct DownArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* uN;       // level l vectors (nullptr at the root: zeros)
     const float* vN;
     int64_t nodes;         // nodes per sequence at level l
@@ -1924,6 +1934,7 @@ __global__ __launch_bounds__(kVecThreads) void k_down_log(DownArgs a) {
     __shared__ float sx[2][kMaxLabels], sw[2][kMaxLabels], sy[2][kMaxLabels];
     __shared__ double red[kVecThreads / kWave];
     const int64_t b = blockIdx.x / a.nodes, k = blockIdx.x % a.nodes;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int C = (int)a.C;
     const int64_t span = (int64_t)1 << a.level, half = span >> 1;
@@ -1967,6 +1978,7 @@ __global__ __launch_bounds__(kVecThreads) void k_down_log(DownArgs a) {
 // (exact: alpha_t, beta_{t+1} are the true messages up to constants, and log Z = const +
 // n_t for every edge t).  The leaves are then streamed once more, 16 bytes per access.
 struct FormArgs {
+    const int32_t* gate;   // [B] compute only the sequences it marks (nullptr: all)
     const float* pot;
     const float* u1;   // level-1 vectors, nullptr when level 1 is the root (D <= 1)
     const float* v1;
@@ -2035,6 +2047,7 @@ __global__ __launch_bounds__(kVecThreads) void k_form_reg(FormArgs a) {
     __shared__ double nrm[2];
     const int64_t npairs = (a.N - 1 + 1) / 2;
     const int64_t b = blockIdx.x / npairs, k = blockIdx.x % npairs;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int C = (int)a.C;
     const int64_t E = a.N - 1;
@@ -2240,6 +2253,7 @@ __global__ __launch_bounds__(kBigThreads) void k_form_big(FormArgs a) {
     extern __shared__ __align__(16) float4 rkeep[];   // [kBigKeep][kW][64]: right-leaf rows
     const int64_t npairs = (a.N - 1 + 1) / 2;
     const int64_t b = blockIdx.x / npairs, k = blockIdx.x % npairs;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t E = a.N - 1;
     const int64_t tL = 2 * k, tR = 2 * k + 1;
@@ -2434,6 +2448,7 @@ __global__ __launch_bounds__(kVecThreads) void k_form_log(FormArgs a) {
     __shared__ double nrm[2];
     const int64_t npairs = (a.N - 1 + 1) / 2;
     const int64_t b = blockIdx.x / npairs, k = blockIdx.x % npairs;
+    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int C = (int)a.C;
     const int64_t E = a.N - 1;
@@ -2570,7 +2585,7 @@ hipError_t up_sweep_vec(const Plan& p, const float* pot, const int32_t* lengths,
     }
     if (e != hipSuccess) return e;
     // the leaves' row and column maxima (shifts of the level-1 products)
-    LeafMaxArgs m{pot, lengths, p.N, p.C, p.lrmax, p.lcmax, p.rbits[0], p.cbits[0], p.bw, p.wide};
+    LeafMaxArgs m{p.gate, pot, lengths, p.N, p.C, p.lrmax, p.lcmax, p.rbits[0], p.cbits[0], p.bw, p.wide};
     // (the LDS-staged kernel for short batches, whose few workgroups are bound by memory
     // latency; with many edges the streaming kernel keeps more bytes in flight per CU)
     if (!kBits && p.C <= kLeafLdsMaxLabels && p.B * p.E <= kLeafLdsMaxEdges) {
@@ -2587,6 +2602,7 @@ hipError_t up_sweep_vec(const Plan& p, const float* pot, const int32_t* lengths,
     const int top = p.scan_level > 0 ? p.scan_level : p.D;   // the levels formed
     for (int l = 1; l <= top; ++l) {
         UpLogArgs a{};
+        a.gate = p.gate;
         if (l == 1) {
             a.ccore = pot; a.cro = nullptr; a.cco = nullptr; a.cnodes = p.E;
             a.cpmr = p.lrmax; a.cpmc = p.lcmax; a.cntile = 1;
@@ -2652,6 +2668,7 @@ hipError_t up_sweep(const Plan& p, const float* pot, const int32_t* lengths, hip
 hipError_t root(const Plan& p, const float* pot, const int32_t* lengths, float* logZ,
                 hipStream_t s) {
     RootArgs r{};
+    r.gate = p.gate;
     if (p.D == 0) {
         r.core = pot; r.ro = nullptr; r.co = nullptr; r.nodes = p.E;
     } else {
@@ -2684,6 +2701,7 @@ hipError_t launch_marginals_tree(const Plan& p, const float* pot, const int32_t*
     if (p.chunk) return launch_chunk_form(p, pot, lengths, marg, s);
     for (int l = p.D; l >= 2; --l) {
         DownArgs d{};
+        d.gate = p.gate;
         d.uN = (l == p.D) ? nullptr : p.u[l];
         d.vN = (l == p.D) ? nullptr : p.v[l];
         d.nodes = p.Np >> l;
@@ -2699,6 +2717,7 @@ hipError_t launch_marginals_tree(const Plan& p, const float* pot, const int32_t*
         if (e != hipSuccess) return e;
     }
     FormArgs f{};
+    f.gate = p.gate;
     f.pot = pot;
     f.u1 = (p.D >= 2) ? p.u[1] : nullptr;
     f.v1 = (p.D >= 2) ? p.v[1] : nullptr;
