@@ -131,8 +131,10 @@ void recur_chunks(int64_t B, int64_t E, int64_t C, int64_t* S, int64_t* K) {
     *K = (E + *S - 1) / *S;
 }
 
-// About what one step of one workgroup's walk takes, without other work on its compute unit
-double walk_step_us(int64_t C) { return C > 128 ? 4.0 : C > 64 ? 1.2 : C > 32 ? 0.5 : 0.35; }
+// About what one step of one workgroup's walk takes, without other work on its compute unit:
+// forward (either semiring), and backward with the marginals
+double walk_step_us(int64_t C) { return C > 128 ? 4.6 : C > 64 ? 1.3 : C > 32 ? 0.6 : 0.4; }
+double walk_back_us(int64_t C) { return C > 128 ? 9.5 : C > 64 ? 2.5 : C > 32 ? 0.9 : 0.5; }
 
 bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, bool masks) {
     *p = Plan{};
@@ -191,7 +193,10 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
             p->rec_gateb = m.take<int32_t>((size_t)B);
         });
         p->gate = bump.take<int32_t>((size_t)B);
-        p->rec_tree = (op == TS_OP_MARGINALS ? 2 : 1) * walk_step_us(C) * p->E > chain_us;
+        // walks that never meet end up walked in order, E dependent steps each way; the tree or
+        // chunk kernels take those sequences where they are faster
+        const double step = walk_step_us(C) + (op == TS_OP_MARGINALS ? walk_back_us(C) : 0.0);
+        p->rec_tree = step * (double)p->E > chain_us;
     };
     if (op == TS_OP_LOGPARTITION || op == TS_OP_MARGINALS) {
         p->chunk = chunk_path(C, masks);
@@ -256,8 +261,8 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
                 p->u[l] = bump.take<float>(n * C);
                 p->v[l] = bump.take<float>(n * C);
             }
-        // (as does the tree, at 8 us per level and sweep)
-        if (recur) place_log(bump.off, 16.0 * D + 2.0 * (double)B * p->E * C * C * C / 40e6);
+        // (as does the tree, 75 above 128 labels, at 8 us per level and sweep)
+        if (recur) place_log(bump.off, 16.0 * D + 2.0 * (double)B * p->E * C * C * C / (C > 128 ? 75e6 : 40e6));
     } else {
         for (int l = 1; l < D; ++l) {   // the root's matrix is never formed
             const size_t n = (size_t)B * (size_t)(Np >> l);

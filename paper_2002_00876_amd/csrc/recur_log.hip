@@ -128,7 +128,8 @@ __device__ __forceinline__ bool same_ratio(const float (&ratio)[2][16], int c, i
 
 // Walks the edges [s, e) of sequence b from the vector v (label j of the lane, see RecCfg) and
 // leaves the last one in v and its exponent in x.  kAgain: stops where it agrees with the
-// stored one, past position `last` (or, at e, with old_end), up to a factor.
+// stored one, past position `last` (or, at e, with old_end), up to a factor.  The first walk
+// looks at the potentials' magnitudes and stops early where they leave the range.
 //
 // Bound: one read of the edges from HBM; per entry about ten issue slots (four of them the
 // exponential).  Loads as in the max semiring's walk: a tile register is reloaded with the
@@ -208,11 +209,14 @@ __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, in
             else
                 *o = acc[cp];
         }
-        if (lane == 0) sm.top[buf][w] = top;
+        // (an infinite top stops every wave: the chunk has left the range)
+        const bool out = !kAgain && __any(big > kRecPotBits);
+        if (lane == 0) sm.top[buf][w] = out ? INFINITY : top;
         if (kLook) publish(buf);
         __syncthreads();
         if (kLook && t > last && same_ratio(sm.ratio[buf], c, F::kNW, rho)) return true;
         const int ex = uniform(exponent_of(row_max(sm.top[buf][c < F::kNW ? c : 0])));
+        if (!kAgain && ex > 127) return true;
         constexpr int kPer = F::kNG / 4;
         float y[kPer];
 #pragma unroll
@@ -245,7 +249,10 @@ __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, in
     // loop; agreement is looked for once per group)
     int t = s;
     for (; t + F::kDepth <= e; t += F::kDepth) {
-        if (step(ring[0], t, std::true_type{})) return {true, t, x - xw + log2((double)rho)};
+        if (step(ring[0], t, std::true_type{})) {
+            bad |= !kAgain;
+            return {true, t, x - xw + log2((double)rho)};
+        }
 #pragma unroll
         for (int i = 1; i < F::kDepth; ++i) step(ring[i], t + i, std::false_type{});
     }
@@ -355,7 +362,7 @@ __device__ void round_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k) {
     const int64_t nbk = a.B * a.K, bk = (int64_t)b * a.K + k;
     const int ver = a.round - 1;   // the predecessor's version, if it is new
     bool changed = false;
-    if (k > 0 && (ver == 0 || a.chg[(size_t)(ver - 1) * nbk + bk - 1]) && !a.bad[bk])
+    if (k > 0 && (ver == 0 || a.chg[(size_t)(ver - 1) * nbk + bk - 1]) && !(a.bad[bk] | a.bad[bk - 1]))
         changed = again_fwd<F>(a, sm, b, k, Eb, a.vend + ((size_t)ver * nbk + bk - 1) * a.C,
                                latest_version(a.chg, nbk, bk, ver), a.round);
     if (threadIdx.x == 0) a.chg[(size_t)ver * nbk + bk] = changed;
@@ -583,6 +590,8 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
         c1 = at.end_exponent();
         c0 = at.exponent(e - 1);
     }
+    constexpr bool kRange = !kAgain && !kForm;   // (with kForm the forward walks have checked)
+    unsigned big = 0;
     float rho;
     // One step, edge t in tile: returns whether the walk ends at position t
     auto step = [&](Tile<F>& tile, int t, auto look) {
@@ -590,6 +599,7 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
         const int from = (t + 1) & 1, to = t & 1;
         // b_{t+1}, scaled by its exponent
         const int ex = uniform(exponent_of(row_max(sm.top[from][c < F::kNW ? c : 0])));
+        if (kRange && ex > 127) return true;
         float bv[F::kCB];
 #pragma unroll
         for (int cp = 0; cp < F::kCP; ++cp) {
@@ -629,10 +639,12 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
 #pragma unroll
             for (int v = 0; v < F::kCB; ++v) {
                 asm volatile("" : "+v"(tile.x[r][v]));
+                if (kRange) big = max(big, fin_bits(tile.x[r][v]));
                 const float p = edge_exp(tile.x[r][v]) * bv[v];
                 sum += p;
                 y[v] = p * wr;
             }
+            if (kRange) asm volatile("" : "+v"(big));
             sums[r] = sum;
             if (kForm) at.store_row(y, ro, soff, r);
             tile_load_row<F>(tile.x[r], rs, voff, r, C);
@@ -652,7 +664,8 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
             const Pair p32 = pair32(__float_as_uint(top));
             top = fmaxf(__uint_as_float(p32.a), __uint_as_float(p32.b));
         }
-        if (lane == 0) sm.top[to][w] = top;
+        const bool out = kRange && __any(big > kRecPotBits);
+        if (lane == 0) sm.top[to][w] = out ? INFINITY : top;
         if (kLook) {
             Ratio ra = ratio_of(own, v, was);
             ra.lo = row_max(-ra.lo);
@@ -672,12 +685,16 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
     for (; t - F::kDepth + 1 >= s; t -= F::kDepth) {
 #pragma unroll
         for (int d = 0; d + 1 < F::kDepth; ++d) step(ring[d], t - d, std::false_type{});
-        if (step(ring[F::kDepth - 1], t - F::kDepth + 1, std::true_type{})) return true;
+        if (step(ring[F::kDepth - 1], t - F::kDepth + 1, std::true_type{})) {
+            bad |= kRange;
+            return true;
+        }
     }
     bool agreed = false;
 #pragma unroll
     for (int d = 0; d + 1 < F::kDepth; ++d)
         if (uniform(t - d >= s)) agreed = step(ring[d], t - d, std::true_type{});
+    bad |= kRange && big > kRecPotBits;
     return agreed;
 }
 
@@ -762,7 +779,8 @@ __device__ void round_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k) {
     const int64_t nbk = a.B * a.K, bk = (int64_t)b * a.K + k;
     const int ver = a.round - 1;
     bool changed = false;
-    if ((k + 1) * a.S < Eb && (ver == 0 || a.chgb[(size_t)(ver - 1) * nbk + bk + 1]) && !a.badb[bk])
+    if ((k + 1) * a.S < Eb && (ver == 0 || a.chgb[(size_t)(ver - 1) * nbk + bk + 1]) &&
+        (kForm || !(a.badb[bk] | a.badb[bk + 1])))
         changed = again_bwd<F, kForm>(a, sm, b, k, Eb, a.vbeg + ((size_t)ver * nbk + bk + 1) * a.C,
                                       latest_version(a.chgb, nbk, bk, ver), a.round);
     if (threadIdx.x == 0) a.chgb[(size_t)ver * nbk + bk] = changed;
