@@ -113,6 +113,30 @@ __device__ __forceinline__ float row_max(float x) {
     return fmaxf(x, dpp_f(x, 0x140));
 }
 
+// The range of the linear log-semiring walks: |l| <= 24 gives E within 2^+-34.7; with 256 labels a step grows
+// the largest entry by less than 2^43, and vectors are scaled by the exponent of the one
+// before, so entries that are not 0 lie within [kRecLow 2^-43, 2^43] of what a step reads and
+// its smallest product stays above 2^-46 - 43 - 35 = 2^-124.
+constexpr float kRecLow = 0x1p-46f;
+constexpr unsigned kRecPotBits = 0x84800000u;   // fin_bits(24)
+
+// Order-preserving magnitude of a finite x; 0 for -inf (one shift-add)
+__device__ __forceinline__ unsigned fin_bits(float x) { return (__float_as_uint(x) << 1) + 0x01000000u; }
+
+// exp(l) to about one rounding for any l of the range: exp2 of the rounded product, corrected
+// by what the rounding dropped.  (-inf is read as a number large enough to give exactly 0.)
+__device__ __forceinline__ float edge_exp(float l) {
+    l = fmaxf(l, -3e37f);
+    const float x = l * 1.4426950408889634f;
+    const float e = __builtin_amdgcn_exp2f(x);
+    return fmaf(e, fmaf(-x, 0.6931471805599453f, l), e);
+}
+
+// floor(log2 x) of a positive normal x; 0 for 0
+__device__ __forceinline__ int exponent_of(float x) {
+    return x > 0.f ? (int)(__float_as_uint(x) >> 23) - 127 : 0;
+}
+
 // Per-lane offsets of a tile's loads: row r of the lane's group, column block cp.  Rows and
 // columns past C read whatever the descriptor's bound leaves (a later row's entries, or 0
 // past the edge): callers give such rows no weight and never use such columns.

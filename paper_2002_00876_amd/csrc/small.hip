@@ -3,6 +3,8 @@
 //   log semiring: up-sweep of semiring matrix products (Sec. 6a / Fig. 3), root
 //   log-sum-exp (log Z), outside sweep and per-edge marginals (Sec. 5.1 gradient identity);
 //   max semiring: float64 up-sweep, forward scores, backpointers and the backtrace.
+// Chains within the range of the linear walks (most), and for the max semiring all short ones,
+// need no tree: one wave per direction walks the chain instead (small_walk_log, walk_max).
 // The arithmetic is that of the multi-launch tree (tree_log.hip / tree_max.hip): node
 // matrices P[a][c] = ro[a] + co[c] + core[a][c] with an exp-shifted fp32 MFMA product
 // (one wave per product), and exact float64 max-plus for Viterbi (the whole workgroup
@@ -20,6 +22,7 @@
 
 #include "device.h"
 #include "internal.h"
+#include "recur.h"
 #include "small.h"
 
 namespace tsc {
@@ -757,6 +760,180 @@ __device__ __forceinline__ void small_log_body(const SmallLogArgs& a, const int6
     zero_padding();
 }
 
+// ================================================================== walks
+// Chains whose potentials stay within the linear range (recur.h) need no tree: one wave walks
+// the forward vector over the edges' exponentials in LDS and another the backward one, C^2
+// work per edge instead of C^3; then all waves form the marginals.  Sequences outside the
+// range take the tree.
+//
+// A step is a chain of dependent instructions of one wave (0.13 us forward, 0.18 us for the
+// max semiring at 8 labels), so a walk's time grows with the length where the tree's grows
+// with its logarithm.  us per call, tree / walk: B = 32, N = 25, C = 20: marginals 20.6 / 13.6,
+// log Z 14.1 / 11.4, Viterbi 20.3 / 11.9; N = 40, C = 8: 19.0 / 10.8, 11.3 / 9.4, 14.6 / 12.0;
+// N = 100, C = 8: 33.3 / 21.1, 16.9 / 18.2, 21.8 / 24.8.  So marginals always walk, and log Z
+// and Viterbi up to kWalkEdges edges (only up to 8 labels fit LDS past that).
+constexpr int kWalkEdges = 80;
+//
+// A vector's entry j sits in lane j of each group of kW lanes; group g of the kGroups sums the
+// rows g * kH .. g * kH + kH - 1 (columns for the backward walk).
+template <int CP>
+struct WalkLanes {
+    static constexpr int kW = CP <= 8 ? 8 : CP <= 16 ? 16 : 32;
+    static constexpr int kGroups = kWave / kW;
+    static constexpr int kH = CP <= 8 ? 1 : CP <= 16 ? 4 : CP / 2;
+};
+// LDS floats: exponentials [E][C][C], forward vectors [E + 1][kW], backward vectors [E + 1][kW]
+template <int CP>
+__host__ __device__ constexpr int64_t walk_floats(int64_t E, int64_t C) {
+    return E * C * C + 2 * (E + 1) * WalkLanes<CP>::kW;
+}
+
+// value of lane l ^ 8 within each row of 16 lanes
+__device__ __forceinline__ float ror8(float x) {
+    const int v = __float_as_int(x);
+    return __int_as_float(__builtin_amdgcn_update_dpp(v, v, 0x128, 0xF, 0xF, false));
+}
+
+// One wave: from ones over Eb edges, forward (v' = v E) or backward (v' = E v).  Every position's
+// vector goes to LDS at vecs, scaled by 2^-x; x is the last one's.  Returns the last vector.
+template <int CP, bool kBack>
+__device__ float walk_linear(int C, int Eb, int vecs, int& x, bool& bad) {
+    using L = WalkLanes<CP>;
+    const int CC = C * C, lane = threadIdx.x % kWave, g = lane / L::kW, j = lane % L::kW;
+    const int jc = min(j, C - 1);
+    int off[L::kH];
+#pragma unroll
+    for (int r = 0; r < L::kH; ++r) {
+        const int i = min(g * L::kH + r, C - 1);
+        off[r] = kBack ? jc * C + i : i * C + jc;
+    }
+    const int first = kBack ? Eb - 1 : 0, dt = kBack ? -1 : 1;
+    float v = j < C ? 1.f : 0.f;
+    if (g == 0) F(vecs + (kBack ? Eb : 0) * L::kW + j) = v;
+    x = 0;
+    float e[L::kH];
+#pragma unroll
+    for (int r = 0; r < L::kH; ++r) e[r] = F(first * CC + off[r]);
+    for (int n = 0; n < Eb; ++n) {
+        const int t = first + n * dt, tn = n + 1 < Eb ? t + dt : t;
+        // lane r of each 16 (the whole group when kH == 1): the weight of its group's row r;
+        // rows past C weigh nothing
+        const float src = __shfl(v, L::kH > 1 ? g * L::kH + min(lane & 15, L::kH - 1) : g, kWave);
+        float en[L::kH];
+#pragma unroll
+        for (int r = 0; r < L::kH; ++r) en[r] = F(tn * CC + off[r]);
+        float m = row_max(v);
+        if constexpr (L::kW == 32) {
+            const Pair p = pair16(__float_as_uint(m));
+            m = fmaxf(__uint_as_float(p.a), __uint_as_float(p.b));
+        }
+        const int ex = uniform(exponent_of(m));
+        float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+        for (int r = 0; r < L::kH; ++r) {
+            const float w = L::kH > 1 ? row_bcast(src, r) : src;
+            if (r & 1) s1 = fmaf(w, e[r], s1);
+            else s0 = fmaf(w, e[r], s0);
+        }
+        float s = s0 + s1;
+        if constexpr (L::kGroups == 8) s += ror8(s);
+        if constexpr (L::kGroups >= 4) {
+            const Pair p = pair16(__float_as_uint(s));
+            s = __uint_as_float(p.a) + __uint_as_float(p.b);
+        }
+        const Pair p = pair32(__float_as_uint(s));
+        s = __uint_as_float(p.a) + __uint_as_float(p.b);
+        v = j < C ? ldexpf(s, -ex) : 0.f;
+        x += ex;
+        bad |= v != 0.f && !(v >= kRecLow && v <= 0x1p60f);
+        if (g == 0) F(vecs + (kBack ? t : t + 1) * L::kW + j) = v;
+#pragma unroll
+        for (int r = 0; r < L::kH; ++r) e[r] = en[r];
+    }
+    return v;
+}
+
+// log Z and the marginals of sequence b by walks; false (nothing written) when its potentials
+// leave the linear range
+template <int CP>
+__device__ __forceinline__ bool small_walk_log(const SmallLogArgs& a, const int64_t b) {
+    using L = WalkLanes<CP>;
+    const int C = a.C, CC = C * C;
+    const int64_t E = a.N - 1;
+    const float* gleaf = a.pot + (size_t)b * E * CC;
+    LeafBatch<kLeafBatch> lb;   // the first loads go out before the length is known
+    lb.load(gleaf, 0, (int)E * CC);
+    const int Eb = (int)(clamp_len(a.lengths, b, a.N) - 1);
+    const int w = uni(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    if (!a.marg && Eb > kWalkEdges) return false;
+    const int n = Eb * CC, fwd = n, bwd = n + (Eb + 1) * L::kW;
+    unsigned big = 0;
+    for (int base = 0; base < n; base += kLeafBatch * kSmallThreads) {
+        if (base > 0) lb.load(gleaf, base, n);
+#pragma unroll
+        for (int u = 0; u < kLeafBatch; ++u) {
+            const int idx = base + u * kSmallThreads + threadIdx.x;
+            if (idx < n) {
+                big = max(big, fin_bits(lb.v[u]));
+                F(idx) = edge_exp(lb.v[u]);
+            }
+        }
+    }
+    if (__syncthreads_or(big > kRecPotBits)) return false;
+    bool bad = false;
+    float lz = 0.f;
+    if (w == 0) {
+        int x;
+        float s = walk_linear<CP, false>(C, Eb, fwd, x, bad);
+        s += dpp_f(s, 0xB1);
+        s += dpp_f(s, 0x4E);
+        s += dpp_f(s, 0x141);
+        if constexpr (L::kW >= 16) s += ror8(s);
+        if constexpr (L::kW == 32) {
+            const Pair p = pair16(__float_as_uint(s));
+            s = __uint_as_float(p.a) + __uint_as_float(p.b);
+        }
+        lz = (float)((log2((double)s) + x) * 0.6931471805599453);
+    } else if (w == 1 && a.marg) {
+        int x;
+        walk_linear<CP, true>(C, Eb, bwd, x, bad);
+    }
+    if (__syncthreads_or(bad)) return false;
+    if (a.logZ && threadIdx.x == 0) a.logZ[b] = lz;
+    if (!a.marg) return true;
+    // mu_t[i][j] = a_t[i] E_t[i][j] b_{t+1}[j] over their sum: one wave per edge, lane l holds
+    // the entries l + 64 q
+    constexpr int kF = (CP * CP + kWave - 1) / kWave;
+    const int di = kWave / C, dj = kWave - di * C;          // the step of 64 entries
+    const int i0 = lane / C, j0 = lane - i0 * C;
+    for (int t = w; t < Eb; t += kSmallWaves) {
+        const int al = fwd + t * L::kW, be = bwd + (t + 1) * L::kW;
+        float y[kF], s = 0.f;
+        int i = i0, j = j0;
+#pragma unroll
+        for (int q = 0; q < kF; ++q) {
+            const int v = lane + kWave * q;
+            y[q] = v < CC ? F(al + min(i, C - 1)) * F(t * CC + min(v, CC - 1)) * F(be + j) : 0.f;
+            s += y[q];
+            j += dj;
+            i += di;
+            const bool wrap = j >= C;
+            j -= wrap ? C : 0;
+            i += wrap ? 1 : 0;
+        }
+        s = wave_sum_fast(s);
+        const float inv = s > 0.f ? 1.f / s : 0.f;
+        float* out = a.marg + ((size_t)b * E + t) * CC;
+#pragma unroll
+        for (int q = 0; q < kF; ++q)
+            if (lane + kWave * q < CC) out[lane + kWave * q] = y[q] * inv;
+    }
+    float* mz = a.marg + ((size_t)b * E + Eb) * CC;         // padding edges are exactly zero
+    const size_t nz = (size_t)(E - Eb) * CC;
+    for (size_t idx = threadIdx.x; idx < nz; idx += kSmallThreads) mz[idx] = 0.f;
+    return true;
+}
+
 // ================================================================== max semiring
 // LDS layout (float offsets): leaves fp32 [E][C][C] | product slots fp64 [E-1][C][C] |
 // last leaf again in fp64 [C][C] | forward scores fp64 [nodes][C] | last scores fp64 [C] |
@@ -992,6 +1169,64 @@ __device__ void wave_edge_argmax(int C, int x, int Nb, uint8_t* bp, int ep, int 
     wave_sync();
 }
 
+// One wave: the forward scores over all Eb edges (fp32 leaves at `leaves`), with the
+// backpointers of every edge and the last scores at dlast: C^2 work per edge, where the tree
+// takes C^3 and its levels' barriers.  Lanes as in walk_linear.
+template <int CP>
+__device__ void walk_max(int C, int Eb, int leaves, uint8_t* bp, int ep, int dlast) {
+    using L = WalkLanes<CP>;
+    const int CC = C * C, lane = threadIdx.x % kWave, g = lane / L::kW, j = lane % L::kW;
+    const int jc = min(j, C - 1);
+    int off[L::kH];
+#pragma unroll
+    for (int r = 0; r < L::kH; ++r) off[r] = leaves + min(g * L::kH + r, C - 1) * C + jc;
+    double v = j < C ? 0.0 : -INFINITY;
+    float e[L::kH];
+#pragma unroll
+    for (int r = 0; r < L::kH; ++r) e[r] = F(off[r]);
+    for (int t = 0; t < Eb; ++t) {
+        const int tn = t + 1 < Eb ? t + 1 : t;
+        const double src = __shfl(v, L::kH > 1 ? g * L::kH + min(lane & 15, L::kH - 1) : g, kWave);
+        float en[L::kH];
+#pragma unroll
+        for (int r = 0; r < L::kH; ++r) en[r] = F(tn * CC + off[r]);
+        double m = -INFINITY;
+        int arg = g * L::kH;
+#pragma unroll
+        for (int r = 0; r < L::kH; ++r) {
+            const double y = (L::kH > 1 ? row_bcast(src, r) : src) + (double)e[r];
+            const bool up = y > m;                 // ties keep the lower row
+            m = up ? y : m;
+            arg = up ? g * L::kH + r : arg;
+        }
+        // across the groups, the lower row winning ties
+        if constexpr (L::kGroups == 8) {
+            const double om = dpp_d<0x128>(m);
+            const int oa = __builtin_amdgcn_update_dpp(arg, arg, 0x128, 0xF, 0xF, false);
+            const bool up = om > m || (om == m && oa < arg);
+            m = up ? om : m;
+            arg = up ? oa : arg;
+        }
+        if constexpr (L::kGroups >= 4) {
+            const PairD p = pair16_d(m);
+            const Pair q = pair16((unsigned)arg);
+            const bool up = p.b > p.a;
+            m = up ? p.b : p.a;
+            arg = (int)(up ? q.b : q.a);
+        }
+        const PairD p = pair32_d(m);
+        const Pair q = pair32((unsigned)arg);
+        const bool up = p.b > p.a;
+        m = up ? p.b : p.a;
+        arg = (int)(up ? q.b : q.a);
+        v = j < C ? m : -INFINITY;
+        if (g == 0 && j < C) bp[j * ep + t] = (uint8_t)arg;
+#pragma unroll
+        for (int r = 0; r < L::kH; ++r) e[r] = en[r];
+    }
+    if (g == 0 && j < C) Dd(dlast + 2 * j) = v;
+}
+
 struct SmallMaxArgs {
     const float* pot;
     const int32_t* lengths;
@@ -1001,51 +1236,11 @@ struct SmallMaxArgs {
     float* score;
 };
 
+// Backpointers and last scores by the tree (the whole workgroup; ends with a barrier)
 template <int CP>
-__device__ __forceinline__ void small_max_body(const SmallMaxArgs& a, const int64_t b) {
-    const int C = a.C;
-    const int64_t E = a.N - 1;
+__device__ __forceinline__ void tree_max(Tree& T, const MaxLayout& ly, int C, int Eb, int w, int lane,
+                                         uint8_t* bp, int ep) {
     const int CC = C * C;
-    const float* gleaf = a.pot + (size_t)b * E * CC;
-    // the first loads of the potentials go out before the length is known
-    LeafBatch<kLeafBatch> lb;
-    lb.load(gleaf, 0, (int)E * CC);
-    const int L = (int)clamp_len(a.lengths, b, a.N), Eb = L - 1;
-    const int w = uni(threadIdx.x / kWave), lane = threadIdx.x % kWave;
-    int32_t* path = a.path + (size_t)b * a.N;
-    // past the length the path is -1 (written last, as the marginals' padding)
-    auto pad_path = [&]() {
-        for (int64_t n = L + threadIdx.x; n < a.N; n += kSmallThreads) path[n] = -1;
-    };
-    if (Eb == 0) {
-        if (threadIdx.x == 0) { path[0] = 0; a.score[b] = 0.f; }
-        pad_path();
-        return;
-    }
-    __shared__ Tree T;
-    const int nodes = (int)small_tree_nodes(Eb);
-    MaxLayout ly;
-    ly.init(C, Eb, nodes);
-    // ---- tree, node table and leaves (fp32, flat)
-    if (w == kSmallWaves - 1) tree_init_wave(T, Eb);
-    build_node_table(Eb, nodes, ly.info);
-    {
-        const int n = Eb * CC;
-        lb.store(ly.leaves, 0, n);
-        for (int base = kLeafBatch * kSmallThreads; base < n; base += kLeafBatch * kSmallThreads) {
-            lb.load(gleaf, base, n);
-            lb.store(ly.leaves, base, n);
-        }
-    }
-    // the root's forward scores (zeros; the root is the last node): nothing else writes the
-    // score vectors before the forward sweep
-    if (w == 0 && lane < C) Dd(ly.vecs + (nodes - 1) * 2 * C + 2 * lane) = 0.0;
-    // padding edges [Eb, ep) of the backpointers: z_t = z_{t+1}
-    if ((int)threadIdx.x < C) {
-        uint8_t* col = reinterpret_cast<uint8_t*>(ts_small_lds + ly.bp) + threadIdx.x * ((Eb + 31) & ~31);
-        for (int t = Eb; t < ((Eb + 31) & ~31); ++t) col[t] = (uint8_t)threadIdx.x;
-    }
-    __syncthreads();
     // the last leaf in fp64 for levels >= 2 (read only after the level-1 barrier)
     for (int i = threadIdx.x; i < CC; i += kSmallThreads)
         Dd(ly.lastc + 2 * i) = (double)F(ly.leaves + (Eb - 1) * CC + i);
@@ -1059,10 +1254,6 @@ __device__ __forceinline__ void small_max_body(const SmallMaxArgs& a, const int6
     }
     // ---- forward scores: u_L = u_N, u_R = u_N (x) L   (root: zeros, set with the leaves)
     auto U = [&](int l, int k) { return ly.vecs + (T.vbase[l] + k) * 2 * C; };
-    // backpointers, column-major with ep (edges rounded up to 32) bytes per column; the
-    // padding edges were set to the identity with the leaves
-    uint8_t* bp = reinterpret_cast<uint8_t*>(ts_small_lds + ly.bp);
-    const int ep = (Eb + 31) & ~31;
     for (int l = T.D; l >= 1; --l) {
         const int nn = uni(T.n[l]), nprev = uni(T.n[l - 1]), vb0 = uni(T.vbase[l - 1]);
         const int ub = uni(U(l, 0)), ub0 = uni(U(l - 1, 0));
@@ -1091,6 +1282,66 @@ __device__ __forceinline__ void small_max_body(const SmallMaxArgs& a, const int6
     }
     if (T.D == 0) {   // one edge: its forward scores are the root's zeros
         if (w == 0) wave_edge_argmax<CP>(C, U(0, 0), ly.leaves, bp, ep, -1, ly.dlast);
+        __syncthreads();
+    }
+}
+
+template <int CP>
+__device__ __forceinline__ void small_max_body(const SmallMaxArgs& a, const int64_t b) {
+    const int C = a.C;
+    const int64_t E = a.N - 1;
+    const int CC = C * C;
+    const float* gleaf = a.pot + (size_t)b * E * CC;
+    // the first loads of the potentials go out before the length is known
+    LeafBatch<kLeafBatch> lb;
+    lb.load(gleaf, 0, (int)E * CC);
+    const int L = (int)clamp_len(a.lengths, b, a.N), Eb = L - 1;
+    const int w = uni(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    int32_t* path = a.path + (size_t)b * a.N;
+    // past the length the path is -1 (written last, as the marginals' padding)
+    auto pad_path = [&]() {
+        for (int64_t n = L + threadIdx.x; n < a.N; n += kSmallThreads) path[n] = -1;
+    };
+    if (Eb == 0) {
+        if (threadIdx.x == 0) { path[0] = 0; a.score[b] = 0.f; }
+        pad_path();
+        return;
+    }
+    __shared__ Tree T;
+    const int nodes = (int)small_tree_nodes(Eb);
+    MaxLayout ly;
+    ly.init(C, Eb, nodes);
+    // ---- leaves (fp32, flat), and for the tree its levels and node table
+    const bool tree = Eb > kWalkEdges;
+    if (tree) {
+        if (w == kSmallWaves - 1) tree_init_wave(T, Eb);
+        build_node_table(Eb, nodes, ly.info);
+    }
+    {
+        const int n = Eb * CC;
+        lb.store(ly.leaves, 0, n);
+        for (int base = kLeafBatch * kSmallThreads; base < n; base += kLeafBatch * kSmallThreads) {
+            lb.load(gleaf, base, n);
+            lb.store(ly.leaves, base, n);
+        }
+    }
+    // the root's forward scores (zeros; the root is the last node): nothing else writes the
+    // score vectors before the forward sweep
+    if (tree && w == 0 && lane < C) Dd(ly.vecs + (nodes - 1) * 2 * C + 2 * lane) = 0.0;
+    // padding edges [Eb, ep) of the backpointers: z_t = z_{t+1}
+    if ((int)threadIdx.x < C) {
+        uint8_t* col = reinterpret_cast<uint8_t*>(ts_small_lds + ly.bp) + threadIdx.x * ((Eb + 31) & ~31);
+        for (int t = Eb; t < ((Eb + 31) & ~31); ++t) col[t] = (uint8_t)threadIdx.x;
+    }
+    __syncthreads();
+    // backpointers, column-major with ep (edges rounded up to 32) bytes per column; the
+    // padding edges were set to the identity with the leaves
+    uint8_t* bp = reinterpret_cast<uint8_t*>(ts_small_lds + ly.bp);
+    const int ep = (Eb + 31) & ~31;
+    if (tree) {
+        tree_max<CP>(T, ly, C, Eb, w, lane, bp, ep);
+    } else {
+        if (w == 0) walk_max<CP>(C, Eb, ly.leaves, bp, ep, ly.dlast);
         __syncthreads();
     }
     // ---- last label (lowest argmax: the first lane holding the maximum), score, backtrace.
@@ -1127,9 +1378,17 @@ __device__ __forceinline__ void small_max_body(const SmallMaxArgs& a, const int6
     pad_path();
 }
 
+// One sequence's log Z and marginals: by walks, or by the tree outside their range
+template <int CP>
+__device__ __forceinline__ void small_log(const SmallLogArgs& a, const int64_t b) {
+    if (small_walk_log<CP>(a, b)) return;
+    __syncthreads();
+    small_log_body<CP>(a, b);
+}
+
 template <int CP>
 __global__ __launch_bounds__(kSmallThreads) void k_small_log(SmallLogArgs a) {
-    small_log_body<CP>(a, blockIdx.x);
+    small_log<CP>(a, blockIdx.x);
 }
 
 template <int CP>
@@ -1144,7 +1403,7 @@ template <int CP>
 __global__ __launch_bounds__(kSmallThreads) void k_small_both(SmallLogArgs la, SmallMaxArgs ma,
                                                              int64_t B) {
     const int64_t g = blockIdx.x;
-    if (g < B) small_log_body<CP>(la, g);
+    if (g < B) small_log<CP>(la, g);
     else small_max_body<CP>(ma, g - B);
 }
 
@@ -1152,12 +1411,20 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_both(SmallLogArgs la, S
 
 // Both layouts are sized for the longest sequence (E = N-1 edges); a shorter sequence
 // uses a prefix of each region, so the offsets computed in the kernels stay inside.
-size_t small_log_lds_bytes(int64_t E, int64_t C) {
+namespace {
+size_t tree_log_lds_bytes(int64_t E, int64_t C) {
     if (E < 1) return 0;
     const int64_t CP = C <= 8 ? 8 : C <= 16 ? 16 : C <= 20 ? 20 : C <= 24 ? 24 : 32;   // as the launcher
     const int64_t coreF = (CP * (CP + 1) + 1) & ~1, slotF = coreF + 4 * CP;
     const int64_t floats = (2 * E - 1) * slotF + small_tree_nodes(E) * 2 * CP + kSmallWaves * 64;
     return sizeof(float) * (size_t)floats + 2 * (size_t)small_tree_nodes(E);   // + node table
+}
+}  // namespace
+
+size_t small_log_lds_bytes(int64_t E, int64_t C) {
+    if (E < 1) return 0;
+    const int64_t walk = C <= 8 ? walk_floats<8>(E, C) : C <= 16 ? walk_floats<16>(E, C) : walk_floats<32>(E, C);
+    return std::max(tree_log_lds_bytes(E, C), sizeof(float) * (size_t)walk);
 }
 
 size_t small_max_lds_bytes(int64_t E, int64_t C) {

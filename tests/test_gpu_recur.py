@@ -72,3 +72,14 @@ def test_no_finite_path_in_a_later_chunk(C):
     pot[1, 190] = -np.inf                       # sequence 1 is cut in two
     pot[2, 250, :, 1:] = -np.inf                # sequence 2 passes through label 0
     check_all(pot, np.array([401, 401, 401], np.int32), f"cut C={C}")
+
+
+@pytest.mark.parametrize("C", [33, 64, 100, 130, 256])
+def test_outside_the_linear_range(C):
+    # sequences that leave the log-semiring walks' range beside one that does not: a large
+    # potential in the middle of a chunk, masks of -1e4, entries far below their vector's largest
+    pot, lens = W.random_case(37000 + C, 4, 200, C, lengths=[200, 200, 150, 200])
+    pot[0, 101, 0, C - 1] = 40.0
+    pot[1, :, :, 0] = -1e4
+    pot[2, 50:60, :, 1:2] -= 23.0
+    check_all(pot, lens, f"range C={C}")
