@@ -114,27 +114,40 @@ int node_scan_level(int64_t E, int D) {
     return level;
 }
 
-// Chunks of the vector recursions: enough workgroups to stream the edges from HBM at full rate
-// (192 of 16 waves above 128 labels, 256 of 8 above 64, 512 of 4 above 32, 1024 below), but
-// not more, and never less than kMinEdges edges: what a walk reads again is what it takes to
-// forget a guessed start, about 10 to 90 edges whatever the chunk's length.  Measured (Viterbi,
-// us per call, at least 48 / 64 / 96 / 128 edges per chunk): C = 64, B = 32, N = 512: 130 /
-// 110 / 118 / 164; C = 128, B = 4, N = 8192: 523 / 538 / 528 / 421 (256 workgroups are the
-// 128); C = 256, B = 16, N = 1024: 994 / 1006 / 959 / 1092 (192 workgroups are 86).
-void recur_chunks(int64_t B, int64_t E, int64_t C, int64_t* S, int64_t* K) {
-    constexpr int64_t kMinEdges = 64;
-    const int64_t slots = C > 128 ? 192 : C > 64 ? 256 : C > 32 ? 512 : 1024;
-    int64_t s = (B * E + slots - 1) / slots;
-    if (s < kMinEdges) s = kMinEdges;
-    const int64_t k = E / s < 1 ? 1 : E / s;
-    *S = (E + k - 1) / k;
-    *K = (E + *S - 1) / *S;
-}
-
 // About what one step of one workgroup's walk takes, without other work on its compute unit:
 // forward (either semiring), and backward with the marginals
 double walk_step_us(int64_t C) { return C > 128 ? 4.6 : C > 64 ? 1.3 : C > 32 ? 0.6 : 0.4; }
 double walk_back_us(int64_t C) { return C > 128 ? 9.5 : C > 64 ? 2.5 : C > 32 ? 0.9 : 0.5; }
+
+// Chunks of the vector recursions: enough workgroups to stream the edges from HBM at full rate
+// (192 of 16 waves above 128 labels, 256 of 8 above 64, 512 of 4 above 32, 1024 below), but
+// not more, and never less than 64 edges: what a walk reads again is what it takes to forget a
+// guessed start, about 10 to 30 edges (10 to 90 in the max semiring) whatever the chunk's
+// length.  Measured (Viterbi, us per call, at least 48 / 64 / 96 / 128 edges per chunk): C =
+// 64, B = 32, N = 512: 130 / 110 / 118 / 164; C = 128, B = 4, N = 8192: 523 / 538 / 528 / 421
+// (256 workgroups are the 128); C = 256, B = 16, N = 1024: 994 / 1006 / 959 / 1092 (192
+// workgroups are 86).
+//
+// Batches that fill less than a quarter of the chip are bound by the steps' latency (above 128
+// labels by what one compute unit can load, some 55 GB/s) and take shorter chunks: half as long,
+// in the log semiring, which forgets sooner, a quarter above 128 labels (log Z of B = 1, N =
+// 126, C = 203: 303 us with 32 edges).  One chunk, which needs no second walk, where the two
+// rounds' launches and the steps walked again would cost more than the steps saved (log Z of
+// one chunk takes half the steps: both directions meet).
+void recur_chunks(int op, int64_t B, int64_t E, int64_t C, int64_t* S, int64_t* K) {
+    const bool log = op != TS_OP_VITERBI;
+    const int64_t slots = C > 128 ? 192 : C > 64 ? 256 : C > 32 ? 512 : 1024;
+    int64_t least = 64;
+    if (B * E < slots * 16) least = log ? (C > 128 ? 16 : 32) : (C > 128 ? 32 : 64);
+    int64_t s = (B * E + slots - 1) / slots;
+    if (s < least) s = least;
+    const int64_t k = E / s < 1 ? 1 : E / s;
+    *S = (E + k - 1) / k;
+    const double one = op == TS_OP_LOGPARTITION ? 0.5 * (double)E : (double)E;
+    const double again = log ? 14 : 40, launches_us = 14;
+    if ((one - (double)*S - again) * walk_step_us(C) < launches_us) *S = E;
+    *K = (E + *S - 1) / *S;
+}
 
 bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, bool masks) {
     *p = Plan{};
@@ -165,7 +178,7 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
     // when they fit there (those kernels, if they run at all, run after the recursions); the
     // gate, which outlives them, is a buffer of its own.
     const bool recur = !force_tree;
-    if (recur) recur_chunks(B, p->E, C, &p->rec_S, &p->rec_K);
+    if (recur) recur_chunks(op, B, p->E, C, &p->rec_S, &p->rec_K);
     const size_t nbk = (size_t)B * p->rec_K, versions = p->rec_K > 1 ? kRecRounds + 2 : 1;
     auto place_recur = [&](size_t used, auto&& place) {
         Bump probe{nullptr};
@@ -175,7 +188,11 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
         else place(bump);
     };
     auto place_log = [&](size_t used, double chain_us) {
-        place_recur(used, [&](Bump& m) {
+        // Exponentials formed beforehand, by the whole chip, while the walks' few workgroups
+        // (at most a quarter of the compute units) would spend most of each step on them
+        // (where they fit the other path's buffers, so that no workspace grows)
+        bool pre = C > 64 && nbk <= 64 && p->E >= 4;
+        auto place = [&](Bump& m) {
             const size_t n = (size_t)B * p->E;
             p->rec_alpha = m.take<float>(n * C);
             p->rec_cx = m.take<int32_t>(n);
@@ -185,13 +202,22 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
             p->rec_shift = m.take<double>(nbk);
             p->rec_last = m.take<int32_t>(nbk);
             p->rec_bad = m.take<int32_t>(nbk);
-            if (op != TS_OP_MARGINALS) return;
-            p->rec_beta = m.take<float>(n * C);
             p->rec_vbeg = m.take<float>(versions * nbk * C);
-            p->rec_chgb = m.take<int32_t>((kRecRounds + 1) * nbk);
             p->rec_badb = m.take<int32_t>(nbk);
             p->rec_gateb = m.take<int32_t>((size_t)B);
-        });
+            p->rec_xbeg = m.take<int32_t>(nbk);
+            if (op == TS_OP_MARGINALS) {
+                p->rec_beta = m.take<float>(n * C);
+                p->rec_chgb = m.take<int32_t>((kRecRounds + 1) * nbk);
+            }
+            p->rec_exp = pre ? m.take<float>(n * C * C) : nullptr;
+        };
+        if (pre) {
+            Bump probe{nullptr};
+            place(probe);
+            pre = probe.off <= used;
+        }
+        place_recur(used, place);
         p->gate = bump.take<int32_t>((size_t)B);
         // walks that never meet end up walked in order, E dependent steps each way; the tree or
         // chunk kernels take those sequences where they are faster

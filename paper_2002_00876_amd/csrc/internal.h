@@ -92,6 +92,8 @@ struct Plan {
     int32_t* rec_chgb = nullptr;   // [kRecRounds + 1][B, K]
     int32_t* rec_badb = nullptr;   // [B, K]
     int32_t* rec_gateb = nullptr;  // [B]
+    int32_t* rec_xbeg = nullptr;   // [B, K]
+    float* rec_exp = nullptr;      // [B, E, C, C] exponentials, where they are formed beforehand
     bool rec_tree = false;         // walks that do not meet are left to the tree
     int32_t* gate = nullptr;       // [B]
     size_t bytes = 0;

@@ -32,6 +32,8 @@ struct RecCfg {
     static constexpr int kG = 64 / LPR, kNG = NW * kG, kRPW = kG * RG, kT = NW * 64;
     static constexpr int kCols = LPR * VEC * CP;   // columns the lanes cover (>= C)
     static constexpr int kCB = CP * VEC;           // columns per lane
+    // whether log-semiring walks can take exponentials formed beforehand (recur_log.hip)
+    static constexpr bool kPre = RG * CP * VEC >= 12 && NW >= 8;
     // edges in flight: up to 64 registers' worth in the layouts of fewer than 16 waves
     static constexpr int kDepth = NW == 16 ? 1 : RG * CP * VEC <= 16 ? 4 : 2;
     static_assert(kRPW <= 16 && kNG % 4 == 0 && kNW <= 16, "a wave's labels fit 16 lanes");

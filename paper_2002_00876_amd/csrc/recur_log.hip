@@ -33,6 +33,7 @@ constexpr size_t kRecBothBytes = (size_t)320 << 20;
 
 struct RecLogArgs {
     const float* pot;
+    float* epot;        // [B, E, C, C] the edges' exponentials, formed beforehand, or nullptr
     const int32_t* lengths;
     int64_t B, N;
     int C, S, K, round;
@@ -55,7 +56,22 @@ struct RecLogArgs {
     float* logZ;        // [B] or nullptr
     int32_t* gate;      // [B]
     bool tree_pending;  // walks that do not meet are left to the tree, too
+    bool meet;          // log Z of one chunk: the two directions meet in its middle
+    int32_t* xbeg;      // [B, K] exponent of the backward walk
 };
+
+template <bool kPre>
+__device__ __forceinline__ float exp_of(float x) {
+    return kPre ? x : edge_exp(x);
+}
+
+// Edges [s, e) of chunk k of a sequence with Eb edges; with a.meet the direction's half
+__device__ __forceinline__ void chunk_edges(const RecLogArgs& a, int k, int Eb, bool back, int& s, int& e) {
+    s = k * a.S;
+    e = uniform(min(s + a.S, Eb));
+    if (a.meet && back) s = uniform(Eb / 2);
+    else if (a.meet) e = uniform(Eb / 2);
+}
 
 template <class F>
 struct FwdLds {
@@ -110,7 +126,7 @@ __device__ __forceinline__ bool same_ratio(const float (&ratio)[2][16], int c, i
 // Bound: one read of the edges from HBM; per entry about ten issue slots (four of them the
 // exponential).  Loads as in the max semiring's walk: a tile register is reloaded with the
 // entry of the edge kDepth further on once it has been used.
-template <class F, bool kAgain>
+template <class F, bool kAgain, bool kPre>
 __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, int e, float& v,
                             int& x, bool& bad, const float* old_end, int old_x, int last) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, C = a.C, CC = C * C;
@@ -125,7 +141,7 @@ __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, in
     if (threadIdx.x == 0) *cx = 0;
 
     const unsigned voff = tile_offset<F>(C);
-    const float* edge = a.pot + (size_t)row * CC;
+    const float* edge = (kPre ? a.epot : a.pot) + (size_t)row * CC;
     Tile<F> ring[F::kDepth];
 #pragma unroll
     for (int i = 0; i < F::kDepth; ++i) {
@@ -137,6 +153,7 @@ __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, in
         }
         edge += CC;
     }
+    constexpr bool kRange = !kAgain && !kPre;
     unsigned big = 0;                              // largest finite magnitude read
     Ratio ra;                                      // at position t
     int xw = 0;                                    // the stored exponent of position t
@@ -170,10 +187,10 @@ __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, in
 #pragma unroll
             for (int i = 0; i < F::kCB; ++i) {
                 asm volatile("" : "+v"(tile.x[r][i]));   // used here, not where it is loaded
-                if (!kAgain) big = max(big, fin_bits(tile.x[r][i]));
-                acc[i] = fmaf(vr, edge_exp(tile.x[r][i]), acc[i]);
+                if (kRange) big = max(big, fin_bits(tile.x[r][i]));
+                acc[i] = fmaf(vr, exp_of<kPre>(tile.x[r][i]), acc[i]);
             }
-            asm volatile("" : "+v"(big));          // (its chain of maxima kept in row order)
+            if (kRange) asm volatile("" : "+v"(big));   // (its chain of maxima kept in row order)
             tile_load_row<F>(tile.x[r], rs, voff, r, C);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -186,7 +203,7 @@ __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, in
                 *o = acc[cp];
         }
         // (an infinite top stops every wave: the chunk has left the range)
-        const bool out = !kAgain && __any(big > kRecPotBits);
+        const bool out = !kAgain && __any(kPre ? bad : big > kRecPotBits);
         if (lane == 0) sm.top[buf][w] = out ? INFINITY : top;
         if (kLook) publish(buf);
         __syncthreads();
@@ -235,7 +252,7 @@ __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, in
 #pragma unroll
     for (int i = 0; i + 1 < F::kDepth; ++i)
         if (uniform(t + i < e)) step(ring[i], t + i, std::false_type{});
-    bad |= big > kRecPotBits;
+    bad |= kRange && big > kRecPotBits;
     if (!kAgain) return {false, s, 0.0};
     publish(e & 1);
     __syncthreads();
@@ -274,7 +291,8 @@ __device__ void finish_fwd(const RecLogArgs& a, int64_t b, int n, const float* v
 template <class F>
 __device__ void first_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k) {
     const int Eb = uniform((int)clamp_len(a.lengths, b, a.N)) - 1;
-    const int s = k * a.S, e = uniform(min(s + a.S, Eb));
+    int s, e;
+    chunk_edges(a, k, Eb, false, s, e);
     if (s >= Eb) {
         if (Eb == 0 && k == 0 && threadIdx.x == 0) {
             a.gate[b] = 0;
@@ -285,9 +303,13 @@ __device__ void first_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k) {
     const int c = threadIdx.x & 15, j = (threadIdx.x >> 6) * F::kRPW + c;
     const bool own = c < F::kRPW && j < a.C;
     float v = own ? 1.f : 0.f;
-    int x;
+    int x = 0;
     bool bad = false;
-    walk_fwd<F, false>(a, sm, b, s, e, v, x, bad, nullptr, 0, s);
+    if (F::kPre && a.epot) {
+        if (s < e) walk_fwd<F, false, F::kPre>(a, sm, b, s, e, v, x, bad, nullptr, 0, s);
+    } else {
+        if (s < e) walk_fwd<F, false, false>(a, sm, b, s, e, v, x, bad, nullptr, 0, s);
+    }
     const int64_t bk = (int64_t)b * a.K + k;
     if (own && (threadIdx.x & 48) == 0) a.vend[(size_t)bk * a.C + j] = v;
     bad = __syncthreads_or(bad);
@@ -297,7 +319,7 @@ __device__ void first_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k) {
         a.last[bk] = s;
         a.bad[bk] = bad;
     }
-    if (a.K > 1) return;
+    if (a.K > 1 || a.meet) return;
     __syncthreads();
     finish_fwd(a, b, 1, a.vend + (size_t)bk * a.C, 0, false);
 }
@@ -315,7 +337,10 @@ __device__ bool again_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k, int 
     bool bad = false;
     const int s = k * a.S, e = uniform(min(s + a.S, Eb));
     const size_t oi = (size_t)old * nbk + bk;
-    const WalkEnd r = walk_fwd<F, true>(a, sm, b, s, e, v, x, bad, a.vend + oi * a.C, a.xend[oi], a.last[bk]);
+    const float* old_end = a.vend + oi * a.C;
+    const WalkEnd r =
+        F::kPre && a.epot ? walk_fwd<F, true, F::kPre>(a, sm, b, s, e, v, x, bad, old_end, a.xend[oi], a.last[bk])
+                          : walk_fwd<F, true, false>(a, sm, b, s, e, v, x, bad, old_end, a.xend[oi], a.last[bk]);
     if (!r.agreed && own && (threadIdx.x & 48) == 0) a.vend[((size_t)ver * nbk + bk) * a.C + j] = v;
     bad = __syncthreads_or(bad);
     if (threadIdx.x == 0) {
@@ -524,14 +549,14 @@ struct FormAt {
 
 // Walks the edges [s, e) of sequence b backwards from the vector in sm.b[e & 1] (its largest
 // entries per wave in sm.top[e & 1]) and, with kForm, writes their marginals; the vector of position s is
-// left in sm.b[s & 1].  kAgain: stops where the vector agrees with the stored one (at s with
+// left in sm.b[s & 1], and the exponent it lacks in x.  kAgain: stops where the vector agrees with the stored one (at s with
 // old_beg) up to a factor, and returns whether it did; the marginals of the edges before that
 // position do not depend on the factor.
 //
 // Bound: one read and one write of the edges (8 C^2 bytes each).  A row's exponentials serve
 // its sum and its marginals at once, so a tile register is stored and reloaded row by row.
-template <class F, bool kAgain, bool kForm>
-__device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s, int e, bool& bad,
+template <class F, bool kAgain, bool kForm, bool kPre>
+__device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s, int e, int& x, bool& bad,
                          const float* old_beg) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, C = a.C, CC = C * C;
     const int gl = lane / F::kLPR, c = lane & 15;
@@ -545,7 +570,7 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
     const FormAt<F> at(a, b, k, C);
     unsigned soff[F::kCP];
     at.store_offsets(soff);
-    const float* edge = a.pot + (size_t)(row0 + e - 1) * CC;
+    const float* edge = (kPre ? a.epot : a.pot) + (size_t)(row0 + e - 1) * CC;
     float* out = a.marg + (size_t)(row0 + e - 1) * CC;
     Tile<F> ring[F::kDepth];
 #pragma unroll
@@ -566,7 +591,9 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
         c1 = at.end_exponent();
         c0 = at.exponent(e - 1);
     }
-    constexpr bool kRange = !kAgain && !kForm;   // (with kForm the forward walks have checked)
+    constexpr bool kFirst = !kAgain && !kForm;   // (with kForm the forward walks have checked)
+    constexpr bool kRange = kFirst && !kPre;
+    x = 0;
     unsigned big = 0;
     float rho;
     // One step, edge t in tile: returns whether the walk ends at position t
@@ -575,7 +602,8 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
         const int from = (t + 1) & 1, to = t & 1;
         // b_{t+1}, scaled by its exponent
         const int ex = uniform(exponent_of(row_max(sm.top[from][c < F::kNW ? c : 0])));
-        if (kRange && ex > 127) return true;
+        if (kFirst && ex > 127) return true;
+        x += ex;
         float bv[F::kCB];
 #pragma unroll
         for (int cp = 0; cp < F::kCP; ++cp) {
@@ -616,7 +644,7 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
             for (int v = 0; v < F::kCB; ++v) {
                 asm volatile("" : "+v"(tile.x[r][v]));
                 if (kRange) big = max(big, fin_bits(tile.x[r][v]));
-                const float p = edge_exp(tile.x[r][v]) * bv[v];
+                const float p = exp_of<kPre>(tile.x[r][v]) * bv[v];
                 sum += p;
                 y[v] = p * wr;
             }
@@ -631,7 +659,7 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
         bad |= mine != 0.f && !(mine >= kRecLow && mine <= 0x1p60f);
         if (own) {
             sm.b[to][i] = v;
-            if (more) a.beta[(size_t)(row0 + t) * C + i] = v;
+            if (more && a.beta) a.beta[(size_t)(row0 + t) * C + i] = v;
         }
         float top = row_max(mine);
         {
@@ -640,7 +668,7 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
             const Pair p32 = pair32(__float_as_uint(top));
             top = fmaxf(__uint_as_float(p32.a), __uint_as_float(p32.b));
         }
-        const bool out = kRange && __any(big > kRecPotBits);
+        const bool out = kFirst && __any(kPre ? bad : big > kRecPotBits);
         if (lane == 0) sm.top[to][w] = out ? INFINITY : top;
         if (kLook) {
             Ratio ra = ratio_of(own, v, was);
@@ -662,7 +690,7 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
 #pragma unroll
         for (int d = 0; d + 1 < F::kDepth; ++d) step(ring[d], t - d, std::false_type{});
         if (step(ring[F::kDepth - 1], t - F::kDepth + 1, std::true_type{})) {
-            bad |= kRange;
+            bad |= kFirst;
             return true;
         }
     }
@@ -712,7 +740,8 @@ __device__ void zero_edges(float* p, int64_t n) {
 template <class F, bool kForm>
 __device__ void first_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k) {
     const int E = (int)a.N - 1, Eb = uniform((int)clamp_len(a.lengths, b, a.N)) - 1;
-    const int s = k * a.S, e = uniform(min(s + a.S, Eb));
+    int s, e;
+    chunk_edges(a, k, Eb, true, s, e);
     if (kForm) {
         if (uniform(a.gate[b] != 0)) return;
         const int CC = a.C * a.C, z = max(s, Eb), ze = min(s + a.S, E);
@@ -722,13 +751,16 @@ __device__ void first_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k) {
     }
     if (s >= Eb) return;
     start_bwd<F>(a, sm, e, nullptr);
+    int x;
     bool bad = false;
-    walk_bwd<F, false, kForm>(a, sm, b, k, s, e, bad, nullptr);
+    if (!kForm && F::kPre && a.epot) walk_bwd<F, false, kForm, !kForm && F::kPre>(a, sm, b, k, s, e, x, bad, nullptr);
+    else walk_bwd<F, false, kForm, false>(a, sm, b, k, s, e, x, bad, nullptr);
     const int64_t bk = (int64_t)b * a.K + k;
     end_bwd<F>(a, sm, s, bk, 0);
     bad = __syncthreads_or(bad);
     if (threadIdx.x == 0) {
         a.badb[bk] = bad;
+        a.xbeg[bk] = x;
         if (a.K == 1) (kForm ? a.gate : a.gateb)[b] = bad;
     }
 }
@@ -739,8 +771,13 @@ __device__ bool again_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int 
     const int64_t nbk = a.B * a.K, bk = (int64_t)b * a.K + k;
     const int s = k * a.S, e = uniform(min(s + a.S, Eb));
     start_bwd<F>(a, sm, e, start);
+    int x;
     bool bad = false;
-    const bool agreed = walk_bwd<F, true, kForm>(a, sm, b, k, s, e, bad, a.vbeg + ((size_t)old * nbk + bk) * a.C);
+    const float* old_beg = a.vbeg + ((size_t)old * nbk + bk) * a.C;
+    const bool agreed =
+        !kForm && F::kPre && a.epot
+            ? walk_bwd<F, true, kForm, !kForm && F::kPre>(a, sm, b, k, s, e, x, bad, old_beg)
+            : walk_bwd<F, true, kForm, false>(a, sm, b, k, s, e, x, bad, old_beg);
     if (!agreed) end_bwd<F>(a, sm, s, bk, ver);
     bad = __syncthreads_or(bad);
     if (bad && threadIdx.x == 0) a.badb[bk] = 1;
@@ -845,7 +882,7 @@ __global__ __launch_bounds__(F::kT, F::kNW == 16 ? 4 : 2) void k_rec_form(RecLog
         return;
     }
     Tile<F> x;
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(uniform(a.pot + ((size_t)b * E + t) * CC), CC);
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(uniform((a.epot ? a.epot : a.pot) + ((size_t)b * E + t) * CC), CC);
     const unsigned voff = tile_offset<F>(C);
 #pragma unroll
     for (int r = 0; r < F::kRG; ++r) tile_load_row<F>(x.x[r], rs, voff, r, C);
@@ -889,9 +926,50 @@ __global__ __launch_bounds__(F::kT, F::kNW == 16 ? 4 : 2) void k_rec_form(RecLog
         const float wr = at.row_of(w, r);
         float y[F::kCB];
 #pragma unroll
-        for (int v = 0; v < F::kCB; ++v) y[v] = edge_exp(x.x[r][v]) * bv[v] * wr;
+        for (int v = 0; v < F::kCB; ++v) {
+            const float e1 = F::kPre && a.epot ? x.x[r][v] : edge_exp(x.x[r][v]);
+            y[v] = e1 * bv[v] * wr;
+        }
         at.store_row(y, ro, soff, r);
     }
+}
+
+// The exponentials of every edge, one workgroup each; an entry outside the range becomes an
+// infinity, which the walks notice
+__global__ __launch_bounds__(256) void k_rec_exp(RecLogArgs a) {
+    const int E = (int)a.N - 1, CC = a.C * a.C;
+    const int b = (int)(blockIdx.x / (unsigned)E), t = (int)blockIdx.x - b * E;
+    if (t >= (int)clamp_len(a.lengths, b, a.N) - 1) return;
+    const size_t at = ((size_t)b * E + t) * CC;
+    const float* from = a.pot + at;
+    float* to = a.epot + at;
+    auto f = [](float x) { return fin_bits(x) > kRecPotBits ? INFINITY : edge_exp(x); };
+    if (CC % 4 == 0) {   // (16-byte aligned edges; eight loads in flight per thread)
+        const int n = CC / 4;
+        for (int i = threadIdx.x; i < n; i += 8 * 256) {
+            float4 x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = ((const float4*)from)[min(i + 256 * u, n - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i + 256 * u < n) ((float4*)to)[i + 256 * u] = make_float4(f(x[u].x), f(x[u].y), f(x[u].z), f(x[u].w));
+        }
+    } else {
+        for (int i = threadIdx.x; i < CC; i += 256) to[i] = f(from[i]);
+    }
+}
+
+// log Z where the two halves of a one-chunk sequence meet: sum_j a_m[j] b_m[j]
+__global__ __launch_bounds__(64) void k_rec_meet(RecLogArgs a) {
+    const int64_t b = blockIdx.x;
+    if (clamp_len(a.lengths, b, a.N) == 1) return;
+    const int lane = threadIdx.x;
+    double tot = 0.0;
+    for (int i = lane; i < a.C; i += 64) tot += (double)a.vend[(size_t)b * a.C + i] * (double)a.vbeg[(size_t)b * a.C + i];
+    tot = wave_sum_d(tot);
+    if (lane != 0) return;
+    a.gate[b] = a.bad[b] | a.badb[b];
+    a.logZ[b] = (float)((log2(tot) + a.xend[b] + a.xbeg[b]) * 0.6931471805599453);
 }
 
 template <class F, Dir dir>
@@ -913,7 +991,19 @@ hipError_t launch_walks(RecLogArgs a, hipStream_t s) {
 }
 
 template <class F>
-hipError_t launch(const RecLogArgs& a, bool both, hipStream_t s) {
+hipError_t launch(RecLogArgs a, bool both, hipStream_t s) {
+    if (!F::kPre) a.epot = nullptr;
+    if (a.epot) {
+        hipLaunchKernelGGL(k_rec_exp, dim3((unsigned)(a.B * (a.N - 1))), dim3(256), 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (a.meet) {
+        const hipError_t e = launch_walks<F, kBoth>(a, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_rec_meet, dim3((unsigned)a.B), dim3(64), 0, s, a);
+        return hipGetLastError();
+    }
     if (!a.marg || !both) {
         hipError_t e = launch_walks<F, kFwd>(a, s);
         return e == hipSuccess && a.marg ? launch_walks<F, kBwdForm>(a, s) : e;
@@ -935,6 +1025,8 @@ hipError_t launch_rec_log(const Plan& p, const float* pot, const int32_t* length
     a.chg = p.rec_chg; a.shift = p.rec_shift; a.last = p.rec_last; a.bad = p.rec_bad;
     a.beta = p.rec_beta; a.vbeg = p.rec_vbeg; a.chgb = p.rec_chgb; a.badb = p.rec_badb;
     a.marg = marg; a.logZ = logZ; a.gate = p.gate; a.gateb = p.rec_gateb; a.tree_pending = p.rec_tree;
+    a.xbeg = p.rec_xbeg; a.epot = p.rec_exp;
+    a.meet = !marg && logZ && p.rec_K == 1 && p.E >= 4;
     const bool both = (size_t)p.B * p.E * p.C * p.C * sizeof(float) <= kRecBothBytes;
     return with_rec_cfg(p.C, [&](auto f) { return launch<decltype(f)>(a, both, s); });
 }
