@@ -176,11 +176,16 @@ __device__ __forceinline__ int latest_version(const int32_t* chg, int64_t nbk, i
 }
 
 // Calls fn(cfg) with the layout for C labels: 16-byte loads when rows are 16-byte aligned
-// (C a multiple of 4), one entry per load otherwise.  Sixteen row groups (eight for the narrow
-// one-entry layouts) give each wave 16 rows and each lane 4 to 64 entries; the layouts between
-// the powers of two (6 and 12 rows per group) keep idle rows below a third.
+// (C a multiple of 4), one entry per load otherwise.  Sixteen row groups (eight or four for the
+// narrow one-entry layouts) give each wave up to 16 rows and each lane 4 to 64 entries; the
+// layouts between the powers of two (6 and 12 rows per group) keep idle rows below a third.
+// Up to 16 labels one wave walks alone: its step has no other wave to wait for (marginals of B
+// = 21, N = 525, C = 9: 73 us with four waves, 50 with one; B = 64, N = 2000, C = 16: 259 with
+// two, 162 with one).  From 17 to 32 one or two waves with longer rows are slower (B = 16, N =
+// 2000, C = 32: 137 against 123).
 template <class Fn>
 hipError_t with_rec_cfg(int64_t C, Fn&& fn) {
+    if (C <= 16) return fn(RecCfg<1, 16, 1, 4, 1>{});
     if (C % 4 == 0) {
         if (C <= 32) return fn(RecCfg<4, 8, 1, 2, 2>{});
         if (C <= 64) return fn(RecCfg<4, 16, 1, 4, 4>{});
