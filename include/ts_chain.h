@@ -234,9 +234,11 @@ ts_status ts_semimarkov_viterbi(const float* sp, const int32_t* lengths, int64_t
  * allocation.  Arguments, outputs, layout and errors are those of ts_chain_marginals without
  * ws / ws_bytes; the kernels and the results are the same.  The call allocates nothing: its
  * scratch is one array of ts_chain_noalloc_scratch_bytes() bytes (64 MiB) per GPU inside the
- * library, held from the first call on that GPU until the process ends.  A problem whose
- * ts_chain_workspace_bytes(TS_OP_MARGINALS, B, N, C) exceeds it returns TS_ERR_BAD_DIM
- * before any device call (the single-launch path for small label sets needs no scratch).
+ * library, held from the first call on that GPU until the process ends.  Every problem whose
+ * ts_chain_workspace_bytes(TS_OP_MARGINALS, B, N, C) does not exceed it is accepted (the
+ * single-launch path for small label sets needs no scratch).  Beyond that, a problem that fits
+ * without the vector recursions' buffers (some with fewer than 32 labels) is computed without
+ * them, and any other returns TS_ERR_BAD_DIM before any device call.
  * Every call on one GPU shares that GPU's array, which keeps the last call's contents (the
  * kernels need none of it cleared): calls that overlap on one GPU, from different streams
  * or threads, race on it and must be serialised by the caller.  TS_CHECK=1 copies the

@@ -149,7 +149,8 @@ void recur_chunks(int op, int64_t B, int64_t E, int64_t C, int64_t* S, int64_t* 
     *K = (E + *S - 1) / *S;
 }
 
-bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, bool masks) {
+bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, bool masks,
+               bool recursions) {
     *p = Plan{};
     p->B = B; p->N = N; p->C = C; p->E = N - 1; p->op = op;
     int64_t cc, bcc;
@@ -177,7 +178,7 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
     // The vector recursions' buffers lie in the first buffers of the tree or chunk path [0, used)
     // when they fit there (those kernels, if they run at all, run after the recursions); the
     // gate, which outlives them, is a buffer of its own.
-    const bool recur = !force_tree;
+    const bool recur = recursions && !force_tree;
     if (recur) recur_chunks(op, B, p->E, C, &p->rec_S, &p->rec_K);
     const size_t nbk = (size_t)B * p->rec_K, versions = p->rec_K > 1 ? kRecRounds + 2 : 1;
     auto place_recur = [&](size_t used, auto&& place) {
@@ -474,6 +475,29 @@ ts_status check_semi(const float* sp, int op, int64_t B, int64_t N, int64_t K, i
 }
 
 }  // namespace
+
+ts_status marginals_call(const float* pot, const int32_t* lengths, int64_t B, int64_t N,
+                         int64_t C, float* logZ, float* marg, void* ws, size_t ws_bytes,
+                         bool recursions, void* stream) {
+    Plan p;
+    ts_status st = check_dims(pot, B, N, C, TS_OP_MARGINALS, &p);
+    if (st == TS_OK && !recursions)
+        make_plan(TS_OP_MARGINALS, B, N, C, nullptr, &p, false, recursions);
+    if (st == TS_OK) st = check_ws(p.bytes, ws, ws_bytes);
+    if (st != TS_OK) return st;
+    if (p.bytes > 0) make_plan(TS_OP_MARGINALS, B, N, C, ws, &p, false, recursions);
+    if (N > 1 && !marg) return fail(TS_ERR_NULL_ARG, "marg is NULL");
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if ((st = check_lengths(lengths, B, N, s)) != TS_OK) return st;
+    if (N == 1) {
+        if (!logZ) return TS_OK;
+        return hip_status(launch_single_token(B, N, C, TS_OP_LOGPARTITION, logZ, nullptr,
+                                              nullptr, s));
+    }
+    if (p.fused) return hip_status(launch_small_log(pot, lengths, B, N, C, logZ, marg, s));
+    return hip_status(log_call(p, pot, lengths, logZ, marg, s));
+}
+
 }  // namespace tsc
 
 using namespace tsc;
@@ -521,19 +545,7 @@ ts_status ts_chain_logpartition(const float* pot, const int32_t* lengths, int64_
 ts_status ts_chain_marginals(const float* pot, const int32_t* lengths, int64_t B, int64_t N,
                              int64_t C, float* logZ, float* marg, void* ws, size_t ws_bytes,
                              void* stream) {
-    Plan p;
-    ts_status st = check_common(pot, B, N, C, TS_OP_MARGINALS, ws, ws_bytes, &p);
-    if (st != TS_OK) return st;
-    if (N > 1 && !marg) return fail(TS_ERR_NULL_ARG, "marg is NULL");
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    if ((st = check_lengths(lengths, B, N, s)) != TS_OK) return st;
-    if (N == 1) {
-        if (!logZ) return TS_OK;
-        return hip_status(launch_single_token(B, N, C, TS_OP_LOGPARTITION, logZ, nullptr,
-                                              nullptr, s));
-    }
-    if (p.fused) return hip_status(launch_small_log(pot, lengths, B, N, C, logZ, marg, s));
-    return hip_status(log_call(p, pot, lengths, logZ, marg, s));
+    return marginals_call(pot, lengths, B, N, C, logZ, marg, ws, ws_bytes, true, stream);
 }
 
 ts_status ts_chain_viterbi(const float* pot, const int32_t* lengths, int64_t B, int64_t N,

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "ts_chain.h"
+
 namespace tsc {
 
 constexpr int kMaxLabels = 256;   // largest C (backpointers are one byte; panels fit LDS)
@@ -135,9 +137,15 @@ int report_error(int code, const char* msg);
 
 // Fills the plan; with base == nullptr only sizes are computed.  Returns false on overflow.
 // masks: keep finiteness bitmasks of the log-semiring nodes (inputs with many structural
-// -inf entries, such as the semi-Markov expansion).
+// -inf entries, such as the semi-Markov expansion).  recursions: take the vector recursions
+// where the size allows it (without them the tree or the chunk kernels compute everything).
 bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p,
-               bool masks = false);
+               bool masks = false, bool recursions = true);
+
+// ts_chain_marginals, with or without the vector recursions
+ts_status marginals_call(const float* pot, const int32_t* lengths, int64_t B, int64_t N,
+                         int64_t C, float* logZ, float* marg, void* ws, size_t ws_bytes,
+                         bool recursions, void* stream);
 
 // ---- launchers (return the first HIP error, hipSuccess otherwise) ----
 hipError_t launch_logz_tree(const Plan& p, const float* pot, const int32_t* lengths,

@@ -59,7 +59,16 @@ ts_status ts_chain_marginals_noalloc(const float* pot, const int32_t* lengths, i
                                      void* stream) {
     // the same validation and plan as ts_chain_marginals, with the workspace size checked
     // against the scratch array before anything else touches the device
-    const size_t need = ts_chain_workspace_bytes(TS_OP_MARGINALS, B, N, C);
+    size_t need = ts_chain_workspace_bytes(TS_OP_MARGINALS, B, N, C);
+    // below 32 labels the vector recursions need two to eight times the workspace of the chunk
+    // kernels, which compute what fits without the recursions only
+    bool recursions = true;
+    Plan bare;
+    if (need > kScratchBytes &&
+        make_plan(TS_OP_MARGINALS, B, N, C, nullptr, &bare, false, /*recursions=*/false)) {
+        recursions = false;
+        need = bare.bytes;
+    }
     if (need > kScratchBytes) {
         // (sizes the plan rejects give 0 and fall through to the call's own checks)
         return report_error(
@@ -76,7 +85,7 @@ ts_status ts_chain_marginals_noalloc(const float* pot, const int32_t* lengths, i
                 TS_ERR_HIP, (std::string("ts_chain_marginals_noalloc: scratch address: ") +
                              hipGetErrorString(e)).c_str());
     }
-    return ts_chain_marginals(pot, lengths, B, N, C, logZ, marg, ws, need, stream);
+    return marginals_call(pot, lengths, B, N, C, logZ, marg, ws, need, recursions, stream);
 }
 
 }  // extern "C"

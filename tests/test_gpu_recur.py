@@ -4,9 +4,10 @@ slowly, or never (the sequences that the tree has to compute), ties, -inf struct
 ragged lengths."""
 import numpy as np
 import pytest
+import torch
 
 from gpu_util import check_all
-from paper_2002_00876_amd import workloads as W
+from paper_2002_00876_amd import binding, workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -83,3 +84,18 @@ def test_outside_the_linear_range(C):
     pot[1, :, :, 0] = -1e4
     pot[2, 50:60, :, 1:2] -= 23.0
     check_all(pot, lens, f"range C={C}")
+
+
+def test_noalloc_without_the_recursions_buffers():
+    # too large for the scratch array with the recursions' buffers, small enough without: the
+    # chunk kernels take it, to the accuracy of the marginals either way (float32 storage of
+    # values in [0, 1] over messages of both paths: 2e-6)
+    B, N, C = 900, 1000, 9
+    assert binding.workspace_bytes(binding.OP_MARGINALS, B, N, C) > binding.noalloc_scratch_bytes()
+    torch.manual_seed(3)
+    pot = torch.randn(B, N - 1, C, C, device="cuda")
+    lens = torch.randint(1, N + 1, (B,), device="cuda", dtype=torch.int32)
+    z1, m1 = binding.marginals(pot, lens)
+    z2, m2 = binding.marginals_noalloc(pot, lens)
+    assert torch.allclose(z1, z2, rtol=1e-6, atol=1e-6)
+    assert (m1 - m2).abs().max().item() <= 2e-6
