@@ -441,8 +441,38 @@ ts_status hip_status(hipError_t e) {
 struct SemiPlan {
     int64_t KC = 0;
     size_t xpot = 0, xout = 0, chain = 0, total = 0;
+    bool walk = false;   // by walks over the segment potentials, without the expanded chain
     Plan base;
 };
+
+// Whether a call is computed by the walks of semi_walk.hip, E dependent steps of one workgroup
+// per sequence and direction, or by the expanded chain, which cuts long sequences into chunks
+// but writes and reads (K C)^2 entries per step (about three passes at 4 TB/s) and launches the
+// recursions and the tree behind them.  Measured (us, log Z / marginals / Viterbi, chain against
+// walk):
+//   B = 32, N = 25, K = 5, C = 20:    58 / 94 / 58     24 / 35 / 28
+//   B = 32, N = 120, K = 5, C = 20:   226 / 256 / 192  96 / 138 / 125
+//   B = 1, N = 40, K = 8, C = 32:     130 / 230 / 174  48 / 74 / 55
+//   B = 1, N = 200, K = 5, C = 20:    89 / 125 / 160   157 / 207 / 205
+//   B = 4, N = 100, K = 4, C = 64:    194 / 307 / 281  205 / 333 / 445
+// The single-launch kernels keep the chains they hold (B = 32, N = 25, K = 2, C = 8: 14 / 17 /
+// 16 against 16 / 21 / 23).
+bool semi_walks(int op, int64_t B, int64_t N, int64_t K, int64_t C, const Plan& chain,
+                size_t ws_bytes) {
+    const char* path = std::getenv("TS_PATH");
+    if (K == 1 || chain.fused || (path && std::strcmp(path, "tree") == 0)) return false;
+    const int64_t E = N - 1, KC = K * C;
+    const bool max = op == TS_OP_VITERBI;
+    double step = max ? (C > 32 ? 4.5 : C > 16 ? 1.0 : 0.8)
+                      : (C > 64 ? 3.0 : C > 32 ? 2.1 : C <= 16 ? 0.45 : KC > 128 ? 1.1 : 0.8);
+    if (op == TS_OP_MARGINALS) step *= 1.25;
+    const double chain_us = (KC > 32 ? 60.0 : 36.0) + 12e-6 / 4.0 * (double)B * E * KC * KC;
+    if (step * (double)E > chain_us) return false;
+    if (max && E * KC > kSemiMaxPath) return false;
+    // (the workspace is the chain's; only that of a few states and edges is too small)
+    SemiWalk w;
+    return semi_walk_bytes(B, N, KC, nullptr, &w) <= ws_bytes;
+}
 
 // Sizes only; returns the reason when the dimensions are out of range, else nullptr.
 const char* plan_semi(int op, int64_t B, int64_t N, int64_t K, int64_t C, SemiPlan* q) {
@@ -464,6 +494,7 @@ const char* plan_semi(int op, int64_t B, int64_t N, int64_t K, int64_t C, SemiPl
     q->chain = x + (op == TS_OP_MARGINALS ? x
                     : op == TS_OP_VITERBI ? align_up(sizeof(int32_t) * B * N) : 0);
     q->total = q->chain + q->base.bytes;
+    q->walk = semi_walks(op, B, N, K, C, q->base, q->total);
     return nullptr;
 }
 
@@ -716,6 +747,11 @@ ts_status ts_semimarkov_logpartition(const float* sp, const int32_t* lengths, in
     if (N == 1) return hip_status(launch_single_token(B, N, C, TS_OP_LOGPARTITION, logZ,
                                                       nullptr, nullptr, s));
     char* w = static_cast<char*>(ws);
+    if (q.walk) {
+        SemiWalk sw;
+        semi_walk_bytes(B, N, q.KC, ws, &sw);
+        return hip_status(launch_semi_walk(sw, sp, lengths, B, N, K, C, logZ, nullptr, s));
+    }
     float* xp = reinterpret_cast<float*>(w + q.xpot);
     hipError_t e = launch_semi_expand(sp, lengths, B, N, K, C, xp, s);
     if (e == hipSuccess) {
@@ -745,6 +781,11 @@ ts_status ts_semimarkov_marginals(const float* sp, const int32_t* lengths, int64
                                               nullptr, s));
     }
     char* w = static_cast<char*>(ws);
+    if (q.walk) {
+        SemiWalk sw;
+        semi_walk_bytes(B, N, q.KC, ws, &sw);
+        return hip_status(launch_semi_walk(sw, sp, lengths, B, N, K, C, logZ, marg, s));
+    }
     float* xp = reinterpret_cast<float*>(w + q.xpot);
     float* xm = reinterpret_cast<float*>(w + q.xout);
     hipError_t e = launch_semi_expand(sp, lengths, B, N, K, C, xp, s);
@@ -773,6 +814,7 @@ ts_status ts_semimarkov_viterbi(const float* sp, const int32_t* lengths, int64_t
     if ((st = check_lengths(lengths, B, N, s)) != TS_OK) return st;
     if (N == 1)
         return hip_status(launch_single_token(B, N, C, TS_OP_VITERBI, nullptr, path, score, s));
+    if (q.walk) return hip_status(launch_semi_max(sp, lengths, B, N, K, C, path, seglen, score, s));
     char* w = static_cast<char*>(ws);
     float* xp = reinterpret_cast<float*>(w + q.xpot);
     int32_t* xs = reinterpret_cast<int32_t*>(w + q.xout);

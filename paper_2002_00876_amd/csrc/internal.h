@@ -184,6 +184,25 @@ hipError_t launch_semi_single(const int32_t* lengths, int64_t B, int64_t N, int6
                               float* logZ, hipStream_t s);
 hipError_t launch_semi_decode(const int32_t* xs, const int32_t* lengths, int64_t B, int64_t N,
                               int64_t C, int32_t* path, int32_t* seglen, hipStream_t s);
+// The same by walks over the segment potentials (semi_walk.hip), for K*C <= 256 states.
+struct SemiWalk {
+    int32_t* bad = nullptr;     // [2][B] the forward, backward walk left the linear range
+    double* lz = nullptr;       // [B] log Z of those sequences
+    int32_t* cx = nullptr;      // [B, N] exponents of alpha
+    float* alpha = nullptr;     // [B, N, KC] linear vectors at every position
+    float* beta = nullptr;      // [B, N, KC]
+    double* alpha64 = nullptr;  // [B, N, KC] logarithms, of the sequences marked in bad
+    double* beta64 = nullptr;   // [B, N, KC]
+};
+// Places the buffers at base (nullptr: sizes only) and returns their bytes.
+size_t semi_walk_bytes(int64_t B, int64_t N, int64_t KC, void* base, SemiWalk* w);
+hipError_t launch_semi_walk(const SemiWalk& w, const float* sp, const int32_t* lengths, int64_t B,
+                            int64_t N, int64_t K, int64_t C, float* logZ, float* marg,
+                            hipStream_t s);
+// at most kSemiMaxPath backpointers (E * K * C) per sequence
+constexpr int64_t kSemiMaxPath = 20480;
+hipError_t launch_semi_max(const float* sp, const int32_t* lengths, int64_t B, int64_t N, int64_t K,
+                           int64_t C, int32_t* path, int32_t* seglen, float* score, hipStream_t s);
 hipError_t launch_logz_sequential(const float* pot, const int32_t* lengths, int64_t B,
                                   int64_t N, int64_t C, float* logZ, hipStream_t s);
 hipError_t launch_log_density(const float* pot, const int32_t* lengths, const int32_t* labels,

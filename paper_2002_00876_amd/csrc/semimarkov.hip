@@ -17,6 +17,7 @@
 //   a segment starts at step t iff r_t = 0, and its length is r_{t+1} + 1.
 // Ordering the states r-major makes the chain's lowest-index backtrace take, at every
 // segment end, the shortest segment and then the lowest previous label among the maximisers.
+// Short sequences are walked without the expansion (semi_walk.hip).
 // One token: log Z = log C (a free label), where the expanded chain would give log(K C).
 #include "device.h"
 #include "internal.h"
