@@ -34,8 +34,13 @@ struct RecCfg {
     static constexpr int kCB = CP * VEC;           // columns per lane
     // whether log-semiring walks can take exponentials formed beforehand (recur_log.hip)
     static constexpr bool kPre = RG * CP * VEC >= 12 && NW >= 8;
-    // edges in flight: up to 64 registers' worth in the layouts of fewer than 16 waves
+    // edges in flight: up to 64 registers' worth in the layouts of fewer than 16 waves.  The max
+    // semiring's walks also have room for two of the 16-wave layouts' smaller tiles (odd label
+    // counts from 65 to 128; Viterbi of B = 32, N = 500, C = 75: 277 us with one, 217 with two;
+    // B = 7, N = 777, C = 101: 356 and 293; B = 4, N = 8192, C = 127: 664 and 630); the log
+    // semiring's would spill registers for 2 to 4%.
     static constexpr int kDepth = NW == 16 ? 1 : RG * CP * VEC <= 16 ? 4 : 2;
+    static constexpr int kDepthMax = NW == 16 && RG * CP * VEC <= 16 ? 2 : kDepth;
     static_assert(kRPW <= 16 && kNG % 4 == 0 && kNW <= 16, "a wave's labels fit 16 lanes");
 };
 

@@ -49,7 +49,7 @@ struct WalkEnd {
 // Bound: one read of the edges from HBM, 4 C^2 bytes each (C = 256: 732 us for 4.29 GB, 5.9
 // TB/s); the arithmetic (convert, add, maximum, compare, select per entry) takes about a third
 // of that time.  The edge's tile is held in registers (64 floats per lane at C = 256), each
-// reloaded with the entry of the edge kDepth further on as soon as it has been used: kDepth
+// reloaded with the entry of the edge kDepthMax further on as soon as it has been used: kDepthMax
 // whole edges per workgroup are in flight (a step at C = 64 is shorter than the memory latency).
 template <class F, bool kAgain>
 __device__ WalkEnd walk(const RecMaxArgs& a, MaxLds<F>& sm, int64_t b, int s, int e, double& d,
@@ -65,9 +65,9 @@ __device__ WalkEnd walk(const RecMaxArgs& a, MaxLds<F>& sm, int64_t b, int s, in
 
     const unsigned voff = tile_offset<F>(C);
     const float* edge = a.pot + (size_t)row * CC;
-    Tile<F> ring[F::kDepth];
+    Tile<F> ring[F::kDepthMax];
 #pragma unroll
-    for (int i = 0; i < F::kDepth; ++i) {
+    for (int i = 0; i < F::kDepthMax; ++i) {
         const __amdgpu_buffer_rsrc_t rs = make_rsrc(uniform(edge), uniform(s + i < e ? CC : 0));
 #pragma unroll
         for (int r = 0; r < F::kRG; ++r) {
@@ -100,7 +100,7 @@ __device__ WalkEnd walk(const RecMaxArgs& a, MaxLds<F>& sm, int64_t b, int s, in
         double dw = d;                             // lane r of each 16: row r of the lane's group
         if constexpr (F::kG > 1) dw = __shfl(d, (gl * F::kRG + c) & 15, kWave);
         // past the chunk's last edge nothing is read: a descriptor of no entries
-        const __amdgpu_buffer_rsrc_t rs = make_rsrc(uniform(edge), uniform(t + F::kDepth < e ? CC : 0));
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(uniform(edge), uniform(t + F::kDepthMax < e ? CC : 0));
         edge += CC;
         double best[F::kCB];
         int arg[F::kCB];
@@ -189,16 +189,16 @@ __device__ WalkEnd walk(const RecMaxArgs& a, MaxLds<F>& sm, int64_t b, int s, in
         }
         return false;
     };
-    // (whole groups of kDepth steps, so that the loads in flight are counted exactly across the
+    // (whole groups of kDepthMax steps, so that the loads in flight are counted exactly across the
     // loop; agreement is looked for once per group)
     int t = s;
-    for (; t + F::kDepth <= e; t += F::kDepth) {
+    for (; t + F::kDepthMax <= e; t += F::kDepthMax) {
         if (step(ring[0], t, std::true_type{})) return {true, t, off};
 #pragma unroll
-        for (int i = 1; i < F::kDepth; ++i) step(ring[i], t + i, std::false_type{});
+        for (int i = 1; i < F::kDepthMax; ++i) step(ring[i], t + i, std::false_type{});
     }
 #pragma unroll
-    for (int i = 0; i + 1 < F::kDepth; ++i)
+    for (int i = 0; i + 1 < F::kDepthMax; ++i)
         if (uniform(t + i < e)) step(ring[i], t + i, std::false_type{});
     if (!kAgain) return {false, s, 0.0};
     publish(e & 1);
