@@ -568,7 +568,7 @@ template <bool kVec, bool kFull>
 __global__ __launch_bounds__(kCT, 4) void k_chunk_up(ChunkUpArgs a) {
     __shared__ ChunkUpSmem sm;
     __shared__ int flag[2];
-    const int64_t b = blockIdx.x / a.nodes, q = blockIdx.x % a.nodes;
+    const int64_t b = blockIdx.x / (unsigned)a.nodes, q = blockIdx.x % (unsigned)a.nodes;
     if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t S = (int64_t)1 << a.lc, t0 = q * S;
@@ -636,7 +636,7 @@ __global__ __launch_bounds__(kCT) void k_chunk_form(ChunkFormArgs a) {
     __shared__ __align__(16) float al[kMaxChunk + 1][kCP];   // alpha_t, shifted (t - t0)
     __shared__ float hs[kMaxChunk];                          // h_t: the shift of alpha_{t+1}
     __shared__ __align__(16) float pm[2][4][kCP], ps[2][4][kCP];   // partial states, ping-pong
-    const int64_t b = blockIdx.x / a.nodes, q = blockIdx.x % a.nodes;
+    const int64_t b = blockIdx.x / (unsigned)a.nodes, q = blockIdx.x % (unsigned)a.nodes;
     if (a.gate && !a.gate[b]) return;
     const int64_t E = a.N - 1, Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t S = (int64_t)1 << a.lc, t0 = q * S;

@@ -77,7 +77,7 @@ __device__ __forceinline__ float fin_abs(float x) { return x == -INFINITY ? 0.f 
 template <bool kVec, bool kBits>
 __global__ __launch_bounds__(256) void k_leaf_max(LeafMaxArgs a) {
     const int64_t E = a.N - 1;
-    const int64_t b = blockIdx.x / E, t = blockIdx.x % E;
+    const int64_t b = blockIdx.x / (unsigned)E, t = blockIdx.x % (unsigned)E;
     if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     if (t >= Eb) return;
@@ -197,7 +197,7 @@ template <bool kVec>
 __global__ __launch_bounds__(kLeafLdsThreads) void k_leaf_max_lds(LeafMaxArgs a) {
     extern __shared__ float T[];   // [C][C + 1]
     const int64_t E = a.N - 1;
-    const int64_t b = blockIdx.x / E, t = blockIdx.x % E;
+    const int64_t b = blockIdx.x / (unsigned)E, t = blockIdx.x % (unsigned)E;
     if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     if (t >= Eb) return;
@@ -350,9 +350,9 @@ __global__ __launch_bounds__(kUpThreads) void k_up_log(UpLogArgs a) {
     const int ntiles = a.ntile * a.ntile;
     const int64_t lid = xcd_node_swizzle(blockIdx.x, ntiles);
     if (lid >= a.nlogical) return;
-    const int tile = (int)(lid % ntiles);
-    const int64_t node = lid / ntiles;
-    const int64_t b = node / a.nodes, k = node % a.nodes;
+    const int tile = (int)((unsigned)lid % (unsigned)ntiles);
+    const int64_t node = (unsigned)lid / (unsigned)ntiles;
+    const int64_t b = (unsigned)node / (unsigned)a.nodes, k = (unsigned)node % (unsigned)a.nodes;
     if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t span = (int64_t)1 << a.level, half = span >> 1;
@@ -736,14 +736,17 @@ __global__ __launch_bounds__(kUpThreads) void k_up_log_small(UpLogArgs a) {
     const int ntiles = a.ntile * a.ntile;
     const int64_t lid = xcd_node_swizzle(blockIdx.x, ntiles);
     if (lid >= a.nlogical) return;
-    const int tile = (int)(lid % ntiles);
-    const int64_t node = lid / ntiles;
-    const int64_t b = node / a.nodes, k = node % a.nodes;
+    const int tile = (int)((unsigned)lid % (unsigned)ntiles);
+    const int64_t node = (unsigned)lid / (unsigned)ntiles;
+    const int64_t b = (unsigned)node / (unsigned)a.nodes, k = (unsigned)node % (unsigned)a.nodes;
     const int C = (int)a.C, nt = a.ntile, cnt = a.cntile;
     const int tm = tile / nt, tn = tile % nt;
     const int a0 = tm * TM, c0 = tn * TM;
     const int tid = threadIdx.x, w = tid / kWave, lane = tid % kWave;
     const int r = lane & 31, h = lane >> 5;
+
+    // (behind the recursions most launches find no sequence marked: no load before this)
+    if (a.gate && !a.gate[b]) return;
 
     // children, clamped into the sequence's node range (the node or its right child may be
     // absent; that is known only once the length has arrived)
@@ -801,7 +804,6 @@ __global__ __launch_bounds__(kUpThreads) void k_up_log_small(UpLogArgs a) {
             if (q < cnt) pm = fmaxf(pm, pp[q]);
     }
 
-    if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t span = (int64_t)1 << a.level, half = span >> 1;
     if (k * span >= Eb) return;   // node absent: all padding
@@ -1056,9 +1058,9 @@ void k_up_log_full(UpLogArgs a) {
     const int ntiles = a.ntile * a.ntile;
     const int64_t lid = xcd_node_swizzle(blockIdx.x, ntiles);
     if (lid >= a.nlogical) return;
-    const int tile = (int)(lid % ntiles);
-    const int64_t node = lid / ntiles;
-    const int64_t b = node / a.nodes, k = node % a.nodes;
+    const int tile = (int)((unsigned)lid % (unsigned)ntiles);
+    const int64_t node = (unsigned)lid / (unsigned)ntiles;
+    const int64_t b = (unsigned)node / (unsigned)a.nodes, k = (unsigned)node % (unsigned)a.nodes;
     if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t span = (int64_t)1 << a.level, half = span >> 1;
@@ -1933,7 +1935,7 @@ template <bool kVec>
 __global__ __launch_bounds__(kVecThreads) void k_down_log(DownArgs a) {
     __shared__ float sx[2][kMaxLabels], sw[2][kMaxLabels], sy[2][kMaxLabels];
     __shared__ double red[kVecThreads / kWave];
-    const int64_t b = blockIdx.x / a.nodes, k = blockIdx.x % a.nodes;
+    const int64_t b = blockIdx.x / (unsigned)a.nodes, k = blockIdx.x % (unsigned)a.nodes;
     if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int C = (int)a.C;
@@ -2046,7 +2048,7 @@ __global__ __launch_bounds__(kVecThreads) void k_form_reg(FormArgs a) {
     __shared__ float pm[kColParts], ps[kColParts], qm[kRowParts], qs[kRowParts];
     __shared__ double nrm[2];
     const int64_t npairs = (a.N - 1 + 1) / 2;
-    const int64_t b = blockIdx.x / npairs, k = blockIdx.x % npairs;
+    const int64_t b = blockIdx.x / (unsigned)npairs, k = blockIdx.x % (unsigned)npairs;
     if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int C = (int)a.C;
@@ -2252,7 +2254,7 @@ __global__ __launch_bounds__(kBigThreads) void k_form_big(FormArgs a) {
     __shared__ double nrm[2];
     extern __shared__ __align__(16) float4 rkeep[];   // [kBigKeep][kW][64]: right-leaf rows
     const int64_t npairs = (a.N - 1 + 1) / 2;
-    const int64_t b = blockIdx.x / npairs, k = blockIdx.x % npairs;
+    const int64_t b = blockIdx.x / (unsigned)npairs, k = blockIdx.x % (unsigned)npairs;
     if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int64_t E = a.N - 1;
@@ -2447,7 +2449,7 @@ __global__ __launch_bounds__(kVecThreads) void k_form_log(FormArgs a) {
     __shared__ double red[kVecThreads / kWave];
     __shared__ double nrm[2];
     const int64_t npairs = (a.N - 1 + 1) / 2;
-    const int64_t b = blockIdx.x / npairs, k = blockIdx.x % npairs;
+    const int64_t b = blockIdx.x / (unsigned)npairs, k = blockIdx.x % (unsigned)npairs;
     if (a.gate && !a.gate[b]) return;
     const int64_t Eb = clamp_len(a.lengths, b, a.N) - 1;
     const int C = (int)a.C;
