@@ -29,10 +29,19 @@ struct RecMaxArgs {
     int32_t* gate;      // [B] sequences left to the tree, or nullptr: none are
 };
 
+// What two walks' scores of one label may differ by, beyond their offset, of the larger one's
+// magnitude: each sum rounds at 2^-53 of it (float32 potentials mostly add exactly), and walks
+// that have met share all but their last few sums.
+constexpr double kMaxTol = 0x1p-50;
+
+// Scores past this magnitude lose the potentials' low bits (2^-25 and below), so they depend on
+// what they are relative to; such sequences are scored from their start, as one walk does.
+constexpr double kMaxScore = 0x1p28;
+
 template <class F>
 struct MaxLds {
     double v[2][F::kNG][F::kCols];      // the row groups' partial maxima, by step parity
-    double off[2][3][16];               // each wave's smallest and largest offset, magnitude
+    double off[2][2][16];               // each wave's bounds of the offset
     uint8_t arg[2][F::kNG][F::kCols];   // the rows (within their group) of the maxima
 };
 
@@ -76,19 +85,19 @@ __device__ WalkEnd walk(const RecMaxArgs& a, MaxLds<F>& sm, int64_t b, int s, in
         }
         edge += CC;
     }
-    double dmn = 0.0, dmx = 0.0, dmg = 0.0;        // this wave's offsets at position t
+    double dlo = 0.0, dhi = 0.0;                   // this wave's bounds at position t
     auto publish = [&](int buf) {
-        if (lane == 0) { sm.off[buf][0][w] = dmn; sm.off[buf][1][w] = dmx; sm.off[buf][2][w] = dmg; }
+        if (lane == 0) { sm.off[buf][0][w] = dlo; sm.off[buf][1][w] = dhi; }
     };
-    // Whether every wave's labels have one offset (after the barrier that follows publish).
-    // Each walk's sums round at 2^-53 of the scores' magnitude per step, far below the 2^-44
-    // allowed; walks that have not met differ by the potentials' own differences.
+    // Whether every wave's labels have one offset (after the barrier that follows publish).  Each
+    // label bounds it by its own two scores, which are known to kMaxTol of their magnitude, and
+    // the walks have met when all bounds share a point: labels that carry a large finite mask
+    // say nothing about the others, and the offset is as exact as the smallest scores.
     auto agree = [&](int buf, double& off) {
         const int i = c < F::kNW ? c : 0;
-        const double mn = -row_max_d(-sm.off[buf][0][i]), mx = row_max_d(sm.off[buf][1][i]);
-        const double mg = row_max_d(sm.off[buf][2][i]);
-        off = mx < mn ? 0.0 : mx;                  // (mx < mn: no label has a finite score)
-        return uniform(mx < mn || mx - mn <= mg * 0x1p-44);
+        const double lo = row_max_d(sm.off[buf][0][i]), hi = -row_max_d(-sm.off[buf][1][i]);
+        off = hi == INFINITY ? 0.0 : 0.5 * (lo + hi);   // (no label has a finite score)
+        return uniform(lo <= hi);
     };
     double off = 0.0;
     // One step, edge t in x: returns whether the walk ends at position t (if asked to look)
@@ -182,10 +191,9 @@ __device__ WalkEnd walk(const RecMaxArgs& a, MaxLds<F>& sm, int64_t b, int s, in
             // one finite and one infinite score never agree
             const bool fin = own && d != -INFINITY && was != -INFINITY;
             const bool odd = own && (d != -INFINITY) != (was != -INFINITY);
-            const double df = d - was;
-            dmn = -row_max_d(odd ? INFINITY : fin ? -df : -INFINITY);
-            dmx = row_max_d(odd ? INFINITY : fin ? df : -INFINITY);
-            dmg = row_max_d(fin ? fmax(fabs(d), fabs(was)) : 0.0);
+            const double df = d - was, tol = kMaxTol * fmax(fabs(d), fabs(was));
+            dlo = row_max_d(odd ? INFINITY : fin ? df - tol : -INFINITY);
+            dhi = -row_max_d(odd ? INFINITY : fin ? -df - tol : -INFINITY);
         }
         return false;
     };
@@ -302,7 +310,8 @@ __global__ __launch_bounds__(F::kT, F::kNW == 16 ? 4 : 2) void k_rec_max_again(R
 
 // One workgroup per sequence: what the rounds have left is walked in order, each chunk from
 // its predecessor's final end scores, or marked for the tree (a.gate); then the last label and
-// the score.  Usually nothing is left; a sequence whose walks never meet is walked whole here.
+// the score.  Usually nothing is left; a sequence whose walks never meet, or whose scores pass
+// kMaxScore (masks that no path avoids), is walked whole here.
 template <class F>
 __global__ __launch_bounds__(F::kT, F::kNW == 16 ? 4 : 2) void k_rec_max_finish(RecMaxArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -336,7 +345,29 @@ __global__ __launch_bounds__(F::kT, F::kNW == 16 ? 4 : 2) void k_rec_max_finish(
     __syncthreads();
     const int64_t bk = (int64_t)b * a.K + n - 1;
     const int ver = changed ? kRecRounds + 1 : latest_version(a.chg, nbk, bk, kRecRounds);
-    finish_sequence(a, b, n, a.vend + ((size_t)ver * nbk + bk) * a.C);
+    const double* v = a.vend + ((size_t)ver * nbk + bk) * a.C;
+    auto past = [](double x) { return x != -INFINITY && fabs(x) > kMaxScore; };
+    bool large = false;
+    for (int k = 1 + threadIdx.x; k < n; k += F::kT) large |= past(a.shift[(int64_t)b * a.K + k]);
+    double best = -INFINITY;
+    for (int i = threadIdx.x & 63; i < a.C; i += 64) best = fmax(best, v[i]);
+    large |= past(wave_max_d(best));
+    if (!__syncthreads_or(large) || n == 1) {   // (one chunk is walked from the start anyway)
+        finish_sequence(a, b, n, v);
+        return;
+    }
+    if (a.gate) {
+        if (threadIdx.x == 0) a.gate[b] = 1;
+        return;
+    }
+    const int c = threadIdx.x & 15, j = (threadIdx.x >> 6) * F::kRPW + c;
+    const bool own = c < F::kRPW && j < a.C;
+    double d = own ? a.vend[(size_t)b * a.K * a.C + j] : -INFINITY;   // chunk 0's end
+    walk<F, false>(a, *(MaxLds<F>*)smem, b, a.S, Eb, d, nullptr, 0);
+    double* end = a.vend + (size_t)bk * a.C;
+    if (own && (threadIdx.x & 48) == 0) end[j] = d;
+    __syncthreads();
+    finish_sequence(a, b, 1, end);
 }
 
 template <class Kernel>

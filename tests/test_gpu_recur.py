@@ -6,7 +6,8 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import check_all
+import oracle
+from gpu_util import check_all, check_logz, say
 from paper_2002_00876_amd import binding, workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -30,6 +31,59 @@ def test_integer_ties(C):
     pot, lens = W.random_case(32000 + C, 3, 400, C, kind="int", int_range=1,
                               lengths=[400, 257, 130])
     check_all(pot, lens, f"ties C={C}")
+
+
+def _check_viterbi(pot, lens, tag):
+    say(f"viterbi {tag}: {pot.shape}")
+    tl = torch.from_numpy(lens).cuda()
+    path, score = binding.viterbi(torch.from_numpy(pot).cuda(), tl)
+    po, so = oracle.viterbi(pot, lens)
+    assert np.array_equal(path.cpu().numpy(), po)
+    check_logz(score.cpu().numpy(), so, "score")
+
+
+# The masks leave the best path alone, so that path and score are those of the other entries,
+# which add exactly in float64; -FLT_MAX sums stay finite there.
+MASKS = [-1e9, -1e12, -1e20, -1e30, float(np.finfo(np.float32).min)]
+
+
+@pytest.mark.parametrize("mask", MASKS)
+@pytest.mark.parametrize("C,N", [(12, 900), (24, 900), (36, 400), (40, 331), (75, 400), (101, 400),
+                                 (128, 600), (131, 300), (256, 300)])
+def test_large_masks(C, N, mask):
+    rng = np.random.default_rng(38000 + C)
+    pot = rng.standard_normal((4, N - 1, C, C)).astype(np.float32)
+    pot[0, :, :, 0] = mask                                       # one label, every edge
+    pot[1, ::3, :, C - 1] = mask                                 # one label, some edges
+    pot[2][rng.random(pot[2].shape) < 0.2] = mask                # random entries
+    pot[3, :, :, 0], pot[3, :, 1, :] = mask, 2 * mask if mask > -1e38 else mask
+    _check_viterbi(pot, np.array([N, N - 1, N, N - 3], np.int32), f"mask {mask:g}")
+
+
+@pytest.mark.parametrize("mask", MASKS[1:])
+@pytest.mark.parametrize("C,N", [(24, 900), (75, 400), (128, 600), (256, 300)])
+def test_masks_on_every_path(C, N, mask):
+    # one edge (in a middle chunk, in the last) masked whole: past it float64 holds the scores to
+    # the mask's last bit only, and decisions are those of sums from the sequence's start
+    pot = np.random.default_rng(38500 + C).integers(-4, 5, (3, N - 1, C, C)).astype(np.float32)
+    mask = np.float32(-2.0 ** round(np.log2(-mask))) if mask > -1e38 else np.float32(mask)
+    pot[0, N // 2] = mask
+    pot[1, N - 3] = mask
+    _check_viterbi(pot, np.array([N, N, N - 20], np.int32), f"masked edge {mask:g}")
+
+
+@pytest.mark.parametrize("mask", [-1e9, -1e20, -1e30])
+def test_large_masks_semi_markov(mask):
+    # long enough for the expanded chain
+    sp, lens = W.semi_case(38800, 3, 500, 4, 12)
+    sp[0, :, :, :, 0] = mask
+    sp[1, ::2, 1, 3, :] = mask
+    assert 499 * 4 * 12 > 20480
+    tl = torch.from_numpy(lens).cuda()
+    path, seglen, score = binding.semi_viterbi(torch.from_numpy(sp).cuda(), tl)
+    po, go, so = oracle.semi_viterbi(sp, lens)
+    assert np.array_equal(path.cpu().numpy(), po) and np.array_equal(seglen.cpu().numpy(), go)
+    check_logz(score.cpu().numpy(), so, "score")
 
 
 def _sticky(seed, B, N, C, stay):
