@@ -82,6 +82,7 @@ struct Plan {
     int32_t* rec_chg = nullptr;    // [kRecRounds (+ 1 in the log semiring)][B, K] which walks
                                    // changed their end
     double* rec_shift = nullptr;   // [B, K]
+    double* rec_ratio = nullptr;   // [B, K] (log semiring)
     int32_t* rec_last = nullptr;   // [B, K]
     // log semiring: vectors and exponents of the forward walks, vectors of the backward ones
     float* rec_alpha = nullptr;    // [B, E, C]
@@ -95,6 +96,9 @@ struct Plan {
     int32_t* rec_badb = nullptr;   // [B, K]
     int32_t* rec_gateb = nullptr;  // [B]
     int32_t* rec_xbeg = nullptr;   // [B, K]
+    int32_t* rec_fine = nullptr;   // [B] log Z is refined (recur_log.hip)
+    int32_t* rec_count = nullptr;  // [B]
+    double* rec_part = nullptr;    // [B, K]
     float* rec_exp = nullptr;      // [B, E, C, C] exponentials, where they are formed beforehand
     bool rec_tree = false;         // walks that do not meet are left to the tree
     int32_t* gate = nullptr;       // [B]

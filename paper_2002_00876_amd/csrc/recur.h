@@ -113,6 +113,12 @@ __device__ __forceinline__ double row_max_d(double x) {
     x = fmax(x, dpp_d(x, 0x141));
     return fmax(x, dpp_d(x, 0x140));
 }
+__device__ __forceinline__ double row_sum_d(double x) {   // (the sum over each row of 16 lanes)
+    x += dpp_d(x, 0xB1);
+    x += dpp_d(x, 0x4E);
+    x += dpp_d(x, 0x141);
+    return x + dpp_d(x, 0x140);
+}
 __device__ __forceinline__ float row_max(float x) {
     x = fmaxf(x, dpp_f(x, 0xB1));
     x = fmaxf(x, dpp_f(x, 0x4E));

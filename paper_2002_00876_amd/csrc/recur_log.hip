@@ -43,7 +43,8 @@ struct RecLogArgs {
     float* vend;        // [kRecRounds + 2][B, K, C] a after the chunk's last edge
     int32_t* xend;      // [kRecRounds + 2][B, K] its exponent
     int32_t* chg;       // [kRecRounds + 1][B, K]
-    double* shift;      // [B, K] what the exponents past `last` lack
+    double* shift;      // [B, K] what the exponents past `last` lack, to float's precision
+    double* ratio;      // [B, K] the ratio whose log2 shift holds
     int32_t* last;      // [B, K] last position that the chunk's latest walk has rewritten
     int32_t* bad;       // [B, K] the chunk has left the range
     // backward
@@ -58,7 +59,16 @@ struct RecLogArgs {
     bool tree_pending;  // walks that do not meet are left to the tree, too
     bool meet;          // log Z of one chunk: the two directions meet in its middle
     int32_t* xbeg;      // [B, K] exponent of the backward walk
+    // log Z once more (k_rec_refine); fine is nullptr where no sequence is long enough
+    int32_t* fine;      // [B] which sequences
+    int32_t* count;     // [B] their chunks that are done
+    double* part;       // [B, K] log2 of the chunks' growth
 };
+
+// log Z of long chains with potentials of log Z near 0 (row-normalised ones, say): each edge's float32
+// arithmetic is off by up to 1e-8 on average (the hardware exponential; C = 8: 2e-9, C = 200: 1e-8),
+// which adds up over the edges and passes 1e-5 of max(|log Z|, 1) past this many.
+constexpr int kRefineEdges = 1000;
 
 template <bool kPre>
 __device__ __forceinline__ float exp_of(float x) {
@@ -78,6 +88,7 @@ struct FwdLds {
     float v[2][F::kNG][F::kCols];   // the row groups' partial sums, by step parity
     float top[2][16];               // each wave's largest entry
     float ratio[2][2][16];          // and smallest and largest ratio to the stored entries
+    double sum[2][16];              // sums of its entries and of the stored ones, where they meet
 };
 template <class F>
 struct BwdLds {
@@ -89,7 +100,8 @@ struct BwdLds {
 struct WalkEnd {
     bool agreed;    // the vector met the stored one
     int last;       // up to this position it was rewritten
-    double off;     // log2 of new over stored, past it
+    int off;        // new over stored, past it: the exponents' difference and the vectors' ratio
+    double ratio;
 };
 
 // Ratios of new to stored entries over a wave's labels; 0 against not 0 never agrees
@@ -106,14 +118,27 @@ __device__ __forceinline__ Ratio ratio_of(bool use, float now, float was) {
     }
     return r;
 }
-// Two walks that have met differ by the rounding of their sums, some 1e-7 per entry; a
-// difference within 2^-20 over all labels cannot grow (the recursions do not expand the ratio
-// of two vectors) and shrinks within a few more edges.
-__device__ __forceinline__ bool same_ratio(const float (&ratio)[2][16], int c, int nw, float& rho) {
+// Whether two walks have met: their vectors differ by the rounding of their sums, some 1e-7 per
+// entry, and a remainder of the guessed start within 2^-20 over all labels is no longer told from
+// it.  It cannot grow (the recursions do not expand the ratio of two vectors).
+__device__ __forceinline__ bool same_ratio(const float (&ratio)[2][16], int c, int nw) {
     const int i = c < nw ? c : 0;
     const float lo = -row_max(-ratio[0][i]), hi = row_max(ratio[1][i]);
-    rho = lo > hi ? 1.f : lo;          // (lo > hi: no label has an entry)
-    return uniform(lo > hi || hi <= lo * (1.f + 0x1p-20f));
+    return uniform(lo > hi || hi <= lo * (1.f + 0x1p-20f));   // (lo > hi: no label has an entry)
+}
+// The ratio of two vectors that have met, whose log2 their chunk adds to log Z: that of their sums,
+// in which roundings and what remains of the guessed start cancel for the most part (in exact
+// arithmetic the remainders of one constant transition matrix with 4 added to its diagonal, C = 8,
+// added up to 1.5e-8 per chunk, those of independent potentials to 1e-9; the smallest or largest
+// ratio would add one-sided errors of up to 2^-20).
+template <class F>
+__device__ __forceinline__ double sum_ratio(FwdLds<F>& sm, float now, float was) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15;
+    const double n = row_sum_d(now), o = row_sum_d(was);
+    if (lane == 0) { sm.sum[0][w] = n; sm.sum[1][w] = o; }
+    __syncthreads();
+    const double sn = row_sum_d(c < F::kNW ? sm.sum[0][c] : 0.0), so = row_sum_d(c < F::kNW ? sm.sum[1][c] : 0.0);
+    return sn > 0.0 && so > 0.0 ? sn / so : 1.0;
 }
 
 // ---- forward
@@ -156,18 +181,19 @@ __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, in
     constexpr bool kRange = !kAgain && !kPre;
     unsigned big = 0;                              // largest finite magnitude read
     Ratio ra;                                      // at position t
-    int xw = 0;                                    // the stored exponent of position t
-    float rho = 1.f;
+    float vs = 0.f;                                // and the stored entry and exponent there
+    int xw = 0;
     auto publish = [&](int buf) {
         if (lane == 0) { sm.ratio[buf][0][w] = ra.lo; sm.ratio[buf][1][w] = ra.hi; }
     };
-    // One step, edge t in tile: returns whether the walk ends at position t (if asked to look)
-    auto step = [&](Tile<F>& tile, int t, auto look) {
-        constexpr bool kLook = kAgain && decltype(look)::value;
+    // One step, edge t in tile: returns whether the walk ends at position t (if asked to look);
+    // whether position t + 1 is looked at
+    auto step = [&](Tile<F>& tile, int t, auto look, auto next) {
+        constexpr bool kLook = kAgain && decltype(look)::value, kNext = kAgain && decltype(next)::value;
         const int buf = t & 1;
         float was = 0.f;                           // the stored entry of position t + 1
         int xn = 0;
-        if (kAgain) {
+        if (kNext) {
             was = t + 1 < e ? al[C] : old_end[own ? j : 0];
             xn = t + 1 < e ? cx[1] : old_x;
         }
@@ -207,7 +233,7 @@ __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, in
         if (lane == 0) sm.top[buf][w] = out ? INFINITY : top;
         if (kLook) publish(buf);
         __syncthreads();
-        if (kLook && t > last && same_ratio(sm.ratio[buf], c, F::kNW, rho)) return true;
+        if (kLook && t > last && same_ratio(sm.ratio[buf], c, F::kNW)) return true;
         const int ex = uniform(exponent_of(row_max(sm.top[buf][c < F::kNW ? c : 0])));
         if (!kAgain && ex > 127) return true;
         constexpr int kPer = F::kNG / 4;
@@ -230,35 +256,54 @@ __device__ WalkEnd walk_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int s, in
             if (own && q == 0) *al = v;
             if (threadIdx.x == 0) *cx = x;
         }
-        if (kAgain) {
+        if (kNext) {
             ra = ratio_of(own, v, was);
             ra.lo = -row_max(-ra.lo);
             ra.hi = row_max(ra.hi);
+            vs = was;
             xw = xn;
         }
         return false;
     };
     // (whole groups of kDepth steps, so that the loads in flight are counted exactly across the
     // loop; agreement is looked for once per group)
-    int t = s;
+    int t = s, met = -1;
     for (; t + F::kDepth <= e; t += F::kDepth) {
-        if (step(ring[0], t, std::true_type{})) {
-            bad |= !kAgain;
-            return {true, t, x - xw + log2((double)rho)};
+        if (step(ring[0], t, std::true_type{}, std::bool_constant<F::kDepth == 1>{})) {
+            met = t;
+            if constexpr (kAgain) break;
+            bad = true;
+            return {true, t, 0, 1.0};
         }
 #pragma unroll
-        for (int i = 1; i < F::kDepth; ++i) step(ring[i], t + i, std::false_type{});
+        for (int i = 1; i + 1 < F::kDepth; ++i) step(ring[i], t + i, std::false_type{}, std::false_type{});
+        if constexpr (F::kDepth > 1)
+            step(ring[F::kDepth - 1], t + F::kDepth - 1, std::false_type{}, std::true_type{});
     }
+    if (met < 0) {
 #pragma unroll
-    for (int i = 0; i + 1 < F::kDepth; ++i)
-        if (uniform(t + i < e)) step(ring[i], t + i, std::false_type{});
-    bad |= kRange && big > kRecPotBits;
-    if (!kAgain) return {false, s, 0.0};
-    publish(e & 1);
-    __syncthreads();
-    if (same_ratio(sm.ratio[e & 1], c, F::kNW, rho))
-        return {true, e - 1, x - xw + log2((double)rho)};
-    return {false, s, 0.0};
+        for (int i = 0; i + 1 < F::kDepth; ++i)
+            if (uniform(t + i < e)) step(ring[i], t + i, std::false_type{}, std::true_type{});
+        bad |= kRange && big > kRecPotBits;
+        if (kAgain) {
+            publish(e & 1);
+            __syncthreads();
+            if (same_ratio(sm.ratio[e & 1], c, F::kNW)) met = e - 1;
+        }
+    }
+    if (!kAgain || met < 0) return {false, s, 0, 1.0};
+    return {true, met, x - xw, sum_ratio(sm, v, own ? vs : 0.f)};
+}
+
+// Stores log Z (lz its log2) and marks it for k_rec_refine
+__device__ __forceinline__ void set_log_z(const RecLogArgs& a, int64_t b, double lz, bool left) {
+    if (!a.logZ) return;
+    const double z = lz * 0.6931471805599453;
+    a.logZ[b] = (float)z;
+    if (!a.fine) return;
+    const double edges = (double)clamp_len(a.lengths, b, a.N) - 1.0;
+    a.fine[b] = !left && edges > kRefineEdges * fmax(fabs(z), 1.0);
+    a.count[b] = 0;
 }
 
 // log Z of sequence b from its final vector v[C] and the chunks' exponents, and whether the
@@ -274,7 +319,8 @@ __device__ void finish_fwd(const RecLogArgs& a, int64_t b, int n, const float* v
         const int ver = k == n - 1 ? ver_last
                         : a.K == 1 ? 0
                                    : latest_version(a.chg, nbk, bk, kRecRounds + 1);
-        sum += a.xend[(size_t)ver * nbk + bk] + a.shift[bk];
+        const double ratio = a.ratio[bk];
+        sum += a.xend[(size_t)ver * nbk + bk] + (a.shift[bk] - (double)__builtin_amdgcn_logf((float)ratio)) + log2(ratio);
         left |= a.bad[bk] != 0;
     }
     for (int i = lane; i < a.C; i += 64) tot += v[i];
@@ -283,7 +329,7 @@ __device__ void finish_fwd(const RecLogArgs& a, int64_t b, int n, const float* v
     left = __any(left);
     if (lane == 0) {
         a.gate[b] = left;
-        if (a.logZ) a.logZ[b] = (float)((sum + log2(tot)) * 0.6931471805599453);
+        set_log_z(a, b, sum + log2(tot), left);
     }
 }
 
@@ -297,6 +343,7 @@ __device__ void first_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k) {
         if (Eb == 0 && k == 0 && threadIdx.x == 0) {
             a.gate[b] = 0;
             if (a.logZ) a.logZ[b] = logf((float)a.C);
+            if (a.fine) a.fine[b] = 0;
         }
         return;
     }
@@ -316,6 +363,7 @@ __device__ void first_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k) {
     if (threadIdx.x == 0) {
         a.xend[bk] = x;
         a.shift[bk] = 0.0;
+        a.ratio[bk] = 1.0;
         a.last[bk] = s;
         a.bad[bk] = bad;
     }
@@ -345,7 +393,8 @@ __device__ bool again_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k, int 
     bad = __syncthreads_or(bad);
     if (threadIdx.x == 0) {
         if (!r.agreed) a.xend[(size_t)ver * nbk + bk] = x;
-        a.shift[bk] = r.off;
+        a.shift[bk] = r.off + (double)__builtin_amdgcn_logf((float)r.ratio);
+        a.ratio[bk] = r.ratio;
         // exponents past `last` are an older walk's; none are once the whole chunk has been
         // walked again
         a.last[bk] = r.last;
@@ -598,7 +647,6 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
     constexpr bool kRange = kFirst && !kPre;
     x = 0;
     unsigned big = 0;
-    float rho;
     // One step, edge t in tile: returns whether the walk ends at position t
     auto step = [&](Tile<F>& tile, int t, auto look) {
         constexpr bool kLook = kAgain && decltype(look)::value;
@@ -686,7 +734,7 @@ __device__ bool walk_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int s
             if (lane == 0) { sm.ratio[to][0][w] = ra.lo; sm.ratio[to][1][w] = ra.hi; }
         }
         __syncthreads();
-        return kLook && same_ratio(sm.ratio[to], c, F::kNW, rho);
+        return kLook && same_ratio(sm.ratio[to], c, F::kNW);
     };
     int t = e - 1;
     for (; t - F::kDepth + 1 >= s; t -= F::kDepth) {
@@ -971,8 +1019,70 @@ __global__ __launch_bounds__(64) void k_rec_meet(RecLogArgs a) {
     for (int i = lane; i < a.C; i += 64) tot += (double)a.vend[(size_t)b * a.C + i] * (double)a.vbeg[(size_t)b * a.C + i];
     tot = wave_sum_d(tot);
     if (lane != 0) return;
-    a.gate[b] = a.bad[b] | a.badb[b];
-    a.logZ[b] = (float)((log2(tot) + a.xend[b] + a.xbeg[b]) * 0.6931471805599453);
+    const bool left = (a.bad[b] | a.badb[b]) != 0;
+    a.gate[b] = left;
+    set_log_z(a, b, log2(tot) + a.xend[b] + a.xbeg[b], left);
+}
+
+// log Z of the marked sequences in float64: one workgroup per chunk walks it from its
+// predecessor's end vector and takes its growth against its own end vector, whose directions are
+// known to some 1e-7, an error of about 1e-8 per chunk (row-normalised, C = 8, N = 65536: 1.4e-4
+// before this, see the tests).  Rare, so simple: four threads share a column.
+__global__ __launch_bounds__(1024) void k_rec_refine(RecLogArgs a) {
+    __shared__ double vec[kMaxLabels], part[4][kMaxLabels], red[2];
+    __shared__ bool done;
+    const int k = (int)(blockIdx.x / (unsigned)a.B), b = (int)(blockIdx.x - k * (unsigned)a.B);
+    if (!a.fine[b]) return;
+    const int Eb = (int)clamp_len(a.lengths, b, a.N) - 1, C = a.C, tid = threadIdx.x;
+    const int s = k * a.S, e = min(s + a.S, Eb);
+    if (s >= Eb) return;
+    const int n = (Eb + a.S - 1) / a.S, j = tid % kMaxLabels, g = tid / kMaxLabels;
+    const int64_t nbk = a.B * a.K, bk = (int64_t)b * a.K + k;
+    auto end_of = [&](int64_t at) {
+        return a.vend + ((size_t)latest_version(a.chg, nbk, at, kRecRounds + 1) * nbk + at) * C;
+    };
+    if (tid < C) vec[tid] = k == 0 ? 1.0 : (double)end_of(bk - 1)[tid];
+    __syncthreads();
+    int x = 0;
+    const float* edge = a.pot + ((size_t)b * (a.N - 1) + s) * C * C;
+    for (int t = s; t < e; ++t, edge += (size_t)C * C) {
+        if ((t - s) % 8 == 7) {   // (a step changes the largest entry by less than 2^43)
+            double m = 0.0;
+            for (int i = tid & 63; i < C; i += 64) m = fmax(m, vec[i]);
+            const int ex = (int)((__double_as_longlong(wave_max_d(m)) >> 52) & 0x7ff) - 1023;
+            __syncthreads();
+            if (tid < C) vec[tid] = ldexp(vec[tid], -ex);
+            x += ex;
+            __syncthreads();
+        }
+        double acc = 0.0;
+        if (j < C)
+            for (int i = g; i < C; i += 4) acc = fma(vec[i], exp((double)edge[(size_t)i * C + j]), acc);
+        part[g][j] = acc;
+        __syncthreads();
+        if (tid < C) vec[tid] = (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+        __syncthreads();
+    }
+    if (tid < 64) {
+        double now = 0.0, was = 0.0;
+        for (int i = tid; i < C; i += 64) {
+            now += vec[i];
+            was += k + 1 < n ? (double)end_of(bk)[i] : 0.0;
+        }
+        now = wave_sum_d(now);
+        was = wave_sum_d(was);
+        if (tid == 0) {
+            a.part[bk] = x + log2(now) - (k + 1 < n ? log2(was) : 0.0);
+            // the last chunk to end adds them up, in order
+            done = __hip_atomic_fetch_add(a.count + b, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+        }
+    }
+    __syncthreads();
+    if (!done || tid >= 64) return;
+    double sum = 0.0;
+    for (int i = tid; i < n; i += 64) sum += a.part[(int64_t)b * a.K + i];
+    sum = wave_sum_d(sum);
+    if (tid == 0) a.logZ[b] = (float)(sum * 0.6931471805599453);
 }
 
 template <class F, Dir dir>
@@ -993,6 +1103,12 @@ hipError_t launch_walks(RecLogArgs a, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t refine(const RecLogArgs& a, hipStream_t s) {
+    if (!a.fine) return hipSuccess;
+    hipLaunchKernelGGL(k_rec_refine, dim3((unsigned)(a.B * a.K)), dim3(1024), 0, s, a);
+    return hipGetLastError();
+}
+
 template <class F>
 hipError_t launch(RecLogArgs a, bool both, hipStream_t s) {
     if (!F::kPre) a.epot = nullptr;
@@ -1005,13 +1121,16 @@ hipError_t launch(RecLogArgs a, bool both, hipStream_t s) {
         const hipError_t e = launch_walks<F, kBoth>(a, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_rec_meet, dim3((unsigned)a.B), dim3(64), 0, s, a);
-        return hipGetLastError();
+        const hipError_t em = hipGetLastError();
+        return em == hipSuccess ? refine(a, s) : em;
     }
     if (!a.marg || !both) {
         hipError_t e = launch_walks<F, kFwd>(a, s);
+        if (e == hipSuccess) e = refine(a, s);
         return e == hipSuccess && a.marg ? launch_walks<F, kBwdForm>(a, s) : e;
     }
     hipError_t e = launch_walks<F, kBoth>(a, s);
+    if (e == hipSuccess) e = refine(a, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_rec_form<F>, dim3((unsigned)(a.B * (a.N - 1))), dim3(F::kT), 0, s, a);
     return hipGetLastError();
@@ -1025,10 +1144,11 @@ hipError_t launch_rec_log(const Plan& p, const float* pot, const int32_t* length
     a.pot = pot; a.lengths = lengths; a.B = p.B; a.N = p.N; a.C = (int)p.C;
     a.S = (int)p.rec_S; a.K = (int)p.rec_K;
     a.alpha = p.rec_alpha; a.cx = p.rec_cx; a.vend = p.rec_vend; a.xend = p.rec_xend;
-    a.chg = p.rec_chg; a.shift = p.rec_shift; a.last = p.rec_last; a.bad = p.rec_bad;
+    a.chg = p.rec_chg; a.shift = p.rec_shift; a.ratio = p.rec_ratio; a.last = p.rec_last; a.bad = p.rec_bad;
     a.beta = p.rec_beta; a.vbeg = p.rec_vbeg; a.chgb = p.rec_chgb; a.badb = p.rec_badb;
     a.marg = marg; a.logZ = logZ; a.gate = p.gate; a.gateb = p.rec_gateb; a.tree_pending = p.rec_tree;
     a.xbeg = p.rec_xbeg; a.epot = p.rec_exp;
+    if (logZ && p.E > kRefineEdges) { a.fine = p.rec_fine; a.count = p.rec_count; a.part = p.rec_part; }
     a.meet = !marg && logZ && p.rec_K == 1 && p.E >= 4;
     const bool both = (size_t)p.B * p.E * p.C * p.C * sizeof(float) <= kRecBothBytes;
     return with_rec_cfg(p.C, [&](auto f) { return launch<decltype(f)>(a, both, s); });

@@ -140,6 +140,42 @@ def test_outside_the_linear_range(C):
     check_all(pot, lens, f"range C={C}")
 
 
+def _normalised(seed, B, N, C):
+    rng = np.random.default_rng(seed)
+    p = rng.standard_normal((B, N - 1, C, C))
+    return (p - np.log(np.exp(p).sum(3, keepdims=True))).astype(np.float32)
+
+
+@pytest.mark.parametrize("B,N,C", [(1, 16384, 8), (1, 65536, 8), (1, 16384, 33), (1, 65536, 33),
+                                   (4, 8192, 20), (1, 8192, 100), (2, 4096, 200), (1100, 2600, 3)])
+def test_row_normalised_potentials(B, N, C):
+    # log Z is near log C however many edges and chunks there are, so that an error per edge or
+    # per chunk shows (the last case has one chunk per sequence)
+    p = _normalised(39000 + C, B, N, C)
+    lens = np.array([N - 7 * (b % 5) for b in range(B)], np.int32)
+    ref = oracle.logpartition(p, lens)
+    labels = np.random.default_rng(1).integers(0, C, (B, N)).astype(np.int32)
+    tp, tl = torch.from_numpy(p).cuda(), torch.from_numpy(lens).cuda()
+    z = binding.logpartition(tp, tl).cpu().numpy()
+    lp = binding.log_density(tp, torch.from_numpy(labels).cuda(), tl).cpu().numpy()
+    say(f"normalised B={B} N={N} C={C}: log Z off by {np.abs(z - ref).max():.1e}")
+    check_logz(z, ref)
+    check_logz(lp, oracle.log_density(p, labels, lens), "log density")
+    if N * C * C <= 1 << 24:
+        z2, _ = binding.marginals(tp, tl)
+        check_logz(z2.cpu().numpy(), ref, "logZ (marginals call)")
+
+
+def test_chunk_scales_have_no_bias():
+    # before log Z is refined: 900 edges in one chunk (among many copies) and in 14 (alone)
+    for C in (8, 33):
+        p = torch.from_numpy(_normalised(39500 + C, 1, 901, C)).cuda()
+        z, _ = binding.marginals(p)
+        many, _ = binding.marginals(p.expand(1024, -1, -1, -1).contiguous())
+        # a rounding per edge at random, 2^-26 per chunk, and the results' own rounding
+        assert abs(z.item() - many[0].item()) <= 2.0 ** -24 * 30 + 14 * 2.0 ** -26 + 2.0 ** -22
+
+
 def test_noalloc_without_the_recursions_buffers():
     # too large for the scratch array with the recursions' buffers, small enough without: the
     # chunk kernels take it, to the accuracy of the marginals either way (float32 storage of
