@@ -412,7 +412,10 @@ __device__ void round_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k) {
     const int64_t nbk = a.B * a.K, bk = (int64_t)b * a.K + k;
     const int ver = a.round - 1;   // the predecessor's version, if it is new
     bool changed = false;
-    if (k > 0 && (ver == 0 || a.chg[(size_t)(ver - 1) * nbk + bk - 1]) && !(a.bad[bk] | a.bad[bk - 1]))
+    // (the predecessor's workgroup may be marking its chunk now: one answer for all waves here.  The
+    // sequence is left to the tree whichever it is.)
+    if (k > 0 && (ver == 0 || a.chg[(size_t)(ver - 1) * nbk + bk - 1]) &&
+        !__syncthreads_or(a.bad[bk] | a.bad[bk - 1]))
         changed = again_fwd<F>(a, sm, b, k, Eb, a.vend + ((size_t)ver * nbk + bk - 1) * a.C,
                                latest_version(a.chg, nbk, bk, ver), a.round);
     if (threadIdx.x == 0) a.chg[(size_t)ver * nbk + bk] = changed;
@@ -844,7 +847,7 @@ __device__ void round_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k) {
     const int ver = a.round - 1;
     bool changed = false;
     if ((k + 1) * a.S < Eb && (ver == 0 || a.chgb[(size_t)(ver - 1) * nbk + bk + 1]) &&
-        (kForm || !(a.badb[bk] | a.badb[bk + 1])))
+        (kForm || !__syncthreads_or(a.badb[bk] | a.badb[bk + 1])))   // (as going forward)
         changed = again_bwd<F, kForm>(a, sm, b, k, Eb, a.vbeg + ((size_t)ver * nbk + bk + 1) * a.C,
                                       latest_version(a.chgb, nbk, bk, ver), a.round);
     if (threadIdx.x == 0) a.chgb[(size_t)ver * nbk + bk] = changed;

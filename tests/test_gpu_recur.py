@@ -140,6 +140,20 @@ def test_outside_the_linear_range(C):
     check_all(pot, lens, f"range C={C}")
 
 
+@pytest.mark.parametrize("C", [9, 24, 36, 64, 75, 100, 130, 256])
+def test_range_left_by_a_second_walk(C):
+    # two label sets without transitions between them, one falling behind by e^-0.3 per edge: every
+    # chunk's first walk stays within the linear range, the walks from true starts leave it
+    N = 700 if C < 100 else 400
+    rng = np.random.default_rng(40000 + C)
+    pot = rng.standard_normal((4, N - 1, C, C)).astype(np.float32)
+    h = C // 2
+    pot[1:, :, :h, h:] = -np.inf
+    pot[1:, :, h:, :h] = -np.inf
+    pot[1:3, :, h:, h:] -= np.float32(0.3)
+    check_all(pot, np.array([N, N, N - 9, N], np.int32), f"falling behind C={C}")
+
+
 def _normalised(seed, B, N, C):
     rng = np.random.default_rng(seed)
     p = rng.standard_normal((B, N - 1, C, C))
