@@ -178,8 +178,13 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
     // The vector recursions' buffers lie in the first buffers of the tree or chunk path [0, used)
     // when they fit there (those kernels, if they run at all, run after the recursions); the
     // gate, which outlives them, is a buffer of its own.
-    const bool recur = recursions && !force_tree;
+    bool recur = recursions && !force_tree;
     if (recur) recur_chunks(op, B, p->E, C, &p->rec_S, &p->rec_K);
+    // (log Z and marginals may walk both directions in one launch)
+    if (recur && !grid_fits((op == TS_OP_VITERBI ? 1 : 2) * B * p->rec_K, rec_threads(C))) {
+        recur = false;
+        p->rec_S = p->rec_K = 0;
+    }
     const size_t nbk = (size_t)B * p->rec_K, versions = p->rec_K > 1 ? kRecRounds + 2 : 1;
     auto place_recur = [&](size_t used, auto&& place) {
         Bump probe{nullptr};
@@ -466,6 +471,7 @@ bool semi_walks(int op, int64_t B, int64_t N, int64_t K, int64_t C, const Plan& 
     const char* path = std::getenv("TS_PATH");
     if (K == 1 || chain.fused || (path && std::strcmp(path, "tree") == 0)) return false;
     const int64_t E = N - 1, KC = K * C;
+    if (!grid_fits(2 * B, 1024) || !grid_fits(B * E, 256)) return false;   // (k_semi_wide, k_semi_form)
     const bool max = op == TS_OP_VITERBI;
     double step = max ? (C > 32 ? 4.5 : C > 16 ? 1.0 : 0.8)
                       : (C > 64 ? 3.0 : C > 32 ? 2.1 : C <= 16 ? 0.45 : KC > 128 ? 1.1 : 0.8);

@@ -105,6 +105,10 @@ struct Plan {
     size_t bytes = 0;
 };
 
+// A launch holds fewer than 2^32 threads: what would pass that takes the kernels with smaller grids
+// (the tree and chunk kernels; the expanded chain of a semi-Markov call).
+inline bool grid_fits(int64_t blocks, int64_t threads) { return blocks * threads < (int64_t)1 << 32; }
+
 constexpr int kRecRounds = 2;  // rounds of walking a chunk again from its predecessor's end
 
 constexpr int kChunkLog = 4;   // chunks of at most 16 edges
@@ -159,6 +163,7 @@ hipError_t launch_marginals_tree(const Plan& p, const float* pot, const int32_t*
                                  float* marg, hipStream_t s);
 hipError_t launch_rec_log(const Plan& p, const float* pot, const int32_t* lengths, float* logZ,
                           float* marg, hipStream_t s);
+int rec_threads(int64_t C);   // threads of a workgroup of the recursions
 hipError_t launch_rec_max(const Plan& p, const float* pot, const int32_t* lengths, float* score,
                           hipStream_t s);
 hipError_t launch_viterbi(const Plan& p, const float* pot, const int32_t* lengths,

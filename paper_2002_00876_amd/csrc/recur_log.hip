@@ -1153,7 +1153,8 @@ hipError_t launch_rec_log(const Plan& p, const float* pot, const int32_t* length
     a.xbeg = p.rec_xbeg; a.epot = p.rec_exp;
     if (logZ && p.E > kRefineEdges) { a.fine = p.rec_fine; a.count = p.rec_count; a.part = p.rec_part; }
     a.meet = !marg && logZ && p.rec_K == 1 && p.E >= 4;
-    const bool both = (size_t)p.B * p.E * p.C * p.C * sizeof(float) <= kRecBothBytes;
+    const bool both = (size_t)p.B * p.E * p.C * p.C * sizeof(float) <= kRecBothBytes &&
+                      grid_fits(p.B * p.E, rec_threads(p.C));   // (k_rec_form)
     return with_rec_cfg(p.C, [&](auto f) { return launch<decltype(f)>(a, both, s); });
 }
 

@@ -397,6 +397,15 @@ hipError_t launch(RecMaxArgs a, hipStream_t s) {
 
 }  // namespace
 
+int rec_threads(int64_t C) {
+    int threads = 0;
+    (void)with_rec_cfg(C, [&](auto f) {
+        threads = decltype(f)::kT;
+        return hipSuccess;
+    });
+    return threads;
+}
+
 hipError_t launch_rec_max(const Plan& p, const float* pot, const int32_t* lengths, float* score,
                           hipStream_t s) {
     RecMaxArgs a{};

@@ -47,6 +47,19 @@ def test_max_labels(L):
     assert L.ts_chain_max_labels() == 256
 
 
+@pytest.mark.parametrize("op,C", [(0, 33), (1, 33), (2, 33), (0, 65), (1, 129), (2, 65)])
+def test_recursions_stay_within_a_launch(L, monkeypatch, op, C):
+    # a launch holds fewer than 2^32 threads, and the recursions' workgroups have up to 1024: past
+    # that a call plans the tree or chunk kernels alone, which reach further
+    ws = binding.workspace_bytes
+    threads = 512 if C < 64 else 1024
+    B = (1 << 32) // threads // (1 if op == 2 else 2)
+    with_recursions, without = ws(op, B - 1, 2, C), ws(op, B, 2, C)
+    monkeypatch.setenv("TS_PATH", "tree")
+    assert with_recursions != ws(op, B - 1, 2, C)
+    assert without == ws(op, B, 2, C)
+
+
 def test_workspace_sizes(L, monkeypatch):
     ws = binding.workspace_bytes
     assert ws(0, 4, 1, 20) == 0 and ws(1, 4, 1, 20) == 0 and ws(2, 4, 1, 20) == 0

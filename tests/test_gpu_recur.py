@@ -190,6 +190,23 @@ def test_chunk_scales_have_no_bias():
         assert abs(z.item() - many[0].item()) <= 2.0 ** -24 * 30 + 14 * 2.0 ** -26 + 2.0 ** -22
 
 
+def test_more_edges_than_a_launch_has_threads_for():
+    # one label, 68.8 million edges: one workgroup of 64 threads per edge would pass 2^32 threads
+    B, N = 8400, 8193
+    g = torch.Generator(device="cuda")
+    g.manual_seed(41000)
+    pot = torch.randn(B, N - 1, 1, 1, generator=g, device="cuda")
+    lens = torch.randint(1, N + 1, (B,), generator=g, device="cuda", dtype=torch.int32)
+    z, m = binding.marginals(pot, lens)
+    on = torch.arange(N - 1, device="cuda")[None] < (lens - 1)[:, None]
+    # each marginal is 1 = a E b / (a' b) with a' = a E: two products, a division, the exponent's power
+    # of two and a' rounded to float32, 5 * 2^-24; padding is exactly 0
+    assert (m[:, :, 0, 0] - on.float()).abs().max().item() <= 5 * 2.0 ** -24
+    assert not m[:, :, 0, 0][~on].any()
+    ref = torch.where(on, pot[:, :, 0, 0].double(), 0.0).sum(1)
+    assert ((z - ref).abs() / ref.abs().clamp(min=1)).max().item() <= 1e-5
+
+
 def test_noalloc_without_the_recursions_buffers():
     # too large for the scratch array with the recursions' buffers, small enough without: the
     # chunk kernels take it, to the accuracy of the marginals either way (float32 storage of
