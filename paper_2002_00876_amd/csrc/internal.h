@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "ts_chain.h"
 
 namespace tsc {
@@ -154,6 +156,25 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p,
 ts_status marginals_call(const float* pot, const int32_t* lengths, int64_t B, int64_t N,
                          int64_t C, float* logZ, float* marg, void* ws, size_t ws_bytes,
                          bool recursions, void* stream);
+
+// Lets kernels take more than 64 KiB of LDS: once per device of the process, as the attribute
+// belongs to the kernel on the current device.
+class AllowLds {
+    std::atomic<uint64_t> done_{0};
+
+public:
+    template <class... K>
+    hipError_t operator()(size_t bytes, K... kernels) {
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+        if (e != hipSuccess || (done_.load(std::memory_order_acquire) & bit)) return e;
+        for (const void* k : {(const void*)kernels...})
+            if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (e == hipSuccess) done_.fetch_or(bit, std::memory_order_release);
+        return e;
+    }
+};
 
 // ---- launchers (return the first HIP error, hipSuccess otherwise) ----
 hipError_t launch_logz_tree(const Plan& p, const float* pot, const int32_t* lengths,

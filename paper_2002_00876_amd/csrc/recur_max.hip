@@ -380,15 +380,10 @@ hipError_t launch_walk(Kernel* kernel, size_t lds, int64_t blocks, int threads,
 template <class F>
 hipError_t launch(RecMaxArgs a, hipStream_t s) {
     constexpr size_t lds = sizeof(MaxLds<F>);
-    static const hipError_t attr = [] {
-        const auto kAttr = hipFuncAttributeMaxDynamicSharedMemorySize;
-        hipError_t e = hipFuncSetAttribute((const void*)k_rec_max<F>, kAttr, (int)lds);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_rec_max_again<F>, kAttr, (int)lds);
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_rec_max_finish<F>, kAttr, (int)lds);
-        return e;
-    }();
-    if (attr != hipSuccess) return attr;
-    hipError_t e = launch_walk(k_rec_max<F>, lds, a.B * a.K, F::kT, a, s);
+    static AllowLds allow;
+    hipError_t e = allow(lds, k_rec_max<F>, k_rec_max_again<F>, k_rec_max_finish<F>);
+    if (e != hipSuccess) return e;
+    e = launch_walk(k_rec_max<F>, lds, a.B * a.K, F::kT, a, s);
     if (a.K == 1) return e;
     for (a.round = 1; e == hipSuccess && a.round <= kRecRounds; ++a.round)
         e = launch_walk(k_rec_max_again<F>, lds, a.B * a.K, F::kT, a, s);

@@ -613,16 +613,6 @@ hipError_t launch_tree(const Plan& p, const float* pot, const int32_t* lengths, 
     return hipGetLastError();
 }
 
-// The decode kernels' tables take up to 64 KiB of LDS and the ends of two 16-byte loads
-hipError_t allow_decode_lds() {
-    static const hipError_t attr = [] {
-        const auto kAttr = hipFuncAttributeMaxDynamicSharedMemorySize;
-        const hipError_t e = hipFuncSetAttribute((const void*)k_dec_map, kAttr, 65536 + 32);
-        return e == hipSuccess ? hipFuncSetAttribute((const void*)k_dec_emit, kAttr, 65536 + 32) : e;
-    }();
-    return attr;
-}
-
 }  // namespace
 
 hipError_t launch_viterbi(const Plan& p, const float* pot, const int32_t* lengths,
@@ -639,7 +629,8 @@ hipError_t launch_viterbi(const Plan& p, const float* pot, const int32_t* length
     // each at most 64 KiB (make_plan), and the bytes around it that stage_bytes copies
     const size_t chunk_bytes = (size_t)std::min(p.dec_chunk, p.E) * C + 32;
     const size_t emit_bytes = std::max(chunk_bytes, (size_t)(p.dec_nchunks - 1) * C + 32);
-    if ((e = allow_decode_lds()) != hipSuccess) return e;
+    static AllowLds allow;
+    if ((e = allow(65536 + 32, k_dec_map, k_dec_emit)) != hipSuccess) return e;
     const dim3 grid((unsigned)(p.B * p.dec_nchunks));
     if (p.dec_nchunks > 1) {
         hipLaunchKernelGGL(k_dec_map, grid, dim3(kDecThreads), chunk_bytes, s, d);

@@ -70,3 +70,19 @@ def test_two_streams_match_single_calls(combined):
                 assert torch.equal(got.cpu(), want), f"rep {rep}, problem {i}: {name} differs"
     say(f"two streams ({'combined call' if combined else 'separate calls'}): 3 rounds bitwise "
         "equal to the single calls")
+
+
+def test_second_device_of_a_process():
+    # kernels with more than 64 KiB of LDS ask for it on every device they run on
+    import torch
+    from paper_2002_00876_amd import binding
+    if torch.cuda.device_count() < 2:
+        pytest.skip("needs two GPUs")
+    pot_h, lens_h = W.random_case(23, 3, 300, 75, lengths=[300, 200, 64])
+    refs = None
+    for d in range(2):
+        with torch.cuda.device(d):
+            pot, lens = torch.from_numpy(pot_h).to(d), torch.from_numpy(lens_h).to(d)
+            outs = [t.cpu() for t in binding.viterbi(pot, lens)]
+        refs = refs or outs
+        assert all(torch.equal(a, b) for a, b in zip(outs, refs))
