@@ -1,10 +1,10 @@
 """Benchmark: tokens/s of batched linear-chain CRF inference on one MI355X.
 
 One timed step is one call of ts_chain_marginals over one batch: log Z and the edge
-marginals (tree up-sweep, root, outside sweep, per-edge marginals), the quantity the
-metric names.  The Viterbi call (max-plus tree, backpointers, backtrace) and the combined
-call ts_chain_marginals_viterbi (the whole hot path: both trees, the Viterbi one on a side
-stream) are timed too and reported in `breakdown`.  --step selects another call as the
+marginals (the forward and backward recursions over all chunks of every sequence and the
+per-edge marginals), the quantity the metric names.  The Viterbi call (max-semiring
+recursion, backpointers, backtrace) and the combined call ts_chain_marginals_viterbi (the
+whole hot path, Viterbi on a side stream) are timed too and reported in `breakdown`.  --step selects another call as the
 timed step; --graph replays a captured HIP graph of it.  Inputs, outputs and workspaces are
 resident in HBM before the timed region.  Prints one JSON line.
 
@@ -23,14 +23,6 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK = 8.0e12          # bytes/s
-MFMA_F32_PEAK = 157.3e12   # flop/s, dense fp32 matrix
-MFMA_BF16_PEAK = 2.5e15    # flop/s, dense bf16 matrix
-# The tree's 128-wide full tiles (C a multiple of 128) multiply float32 operands as three bf16
-# parts each, six bf16 products per float32 product: their float32-equivalent peak
-MFMA_BF16X6_PEAK = MFMA_BF16_PEAK / 6
-# fp64 vector: 78.6 TFLOP/s counts an FMA as two flops, i.e. 256 CUs x 4 SIMDs x 16 lanes x
-# 2.4 GHz = 39.3e12 lane-instructions/s; a max-plus pair is two of them (add, max)
-VALU_F64_OPS_PEAK = 39.3e12
 
 PAPER_CONTEXT_TOKENS_PER_S = 390e3   # Table 1, K80, batch 32, N=25, C=20 (context only)
 
@@ -73,52 +65,41 @@ def parse():
 
 
 def algorithmic(pot, lens):
-    """Algorithmic HBM bytes and semiring work of one call of each entry point."""
+    """Algorithmic HBM bytes and operations of one call of each entry point: per entry of a valid
+    edge a product and a sum for each recursion (an add and a maximum for Viterbi) and two
+    products for a marginal."""
     B, E, C, _ = pot.shape
     Eb = (lens.astype("int64") - 1)
     valid = int(Eb.sum())
-    products = int((Eb - 1).clip(min=0).sum())          # tree products, C^3 pairs each
     marg_bytes = 4 * C * C * valid + 4 * C * C * B * E + 4 * B      # read valid, write all
     vit_bytes = 4 * C * C * valid + 4 * B * (E + 1) + 4 * B          # read valid, path+score
     step_bytes = marg_bytes + vit_bytes - 4 * C * C * valid         # one read of the input
-    pairs = products * C ** 3
-    return dict(marg_bytes=marg_bytes, vit_bytes=vit_bytes, step_bytes=step_bytes, pairs=pairs,
-                marg_flops=2 * pairs, vit_ops=2 * pairs, valid_edges=valid)
+    entries = valid * C * C
+    return dict(marg_bytes=marg_bytes, vit_bytes=vit_bytes, step_bytes=step_bytes,
+                marg_flops=6 * entries, vit_ops=2 * entries, valid_edges=valid)
 
 
 def measured_traffic(kernel, workload):
     """HBM bytes per launch of `kernel` on `workload` from a committed rocprofv3 summary
     (FETCH_SIZE + WRITE_SIZE, copy-calibrated) in profiles/, or None when there is none or
-    the kernel's source has changed since the counters were taken."""
+    the kernel's source has changed since the counters were taken.  A summary holds blocks of
+    `key = value` lines, each beginning with the kernel."""
     import glob
     for path in sorted(glob.glob(os.path.join(ROOT, "profiles", "*.md"))):
-        kv = {}
+        blocks = []
         for line in open(path):
             if " = " in line:
                 k, v = line.strip().split(" = ", 1)
-                kv[k] = v
-        if kv.get("kernel") != kernel or kv.get("workload") != workload:
-            continue
-        src = os.path.join(ROOT, kv.get("source", ""))
-        if not os.path.isfile(src):
-            return None
-        if code_hash(src) != kv.get("source_sha256"):
-            return None
-        return int(kv["traffic_bytes_per_launch"])
+                if k == "kernel" or not blocks:
+                    blocks.append({})
+                blocks[-1][k] = v
+        for kv in blocks:
+            if kv.get("kernel") != kernel or kv.get("workload") != workload:
+                continue
+            src = os.path.join(ROOT, kv.get("source", ""))
+            if os.path.isfile(src) and code_hash(src) == kv.get("source_sha256"):
+                return int(kv["traffic_bytes_per_launch"])
     return None
-
-
-def node_scan_level(E, D):
-    """The level at which log Z's up-sweep stops for the recursion over that level's nodes
-    (at most 128 labels on the tree), 0 for the tree to the root; the same cost model as the
-    workspace plan (node_scan_level in paper_2002_00876_amd/csrc/api.cpp)."""
-    level_us, step_us, scan_us, root_us = 12.0, 1.0, 5.0, 10.0
-    best, level = D * level_us + root_us, 0
-    for l in range(1, D):
-        t = l * level_us + ((E + (1 << l) - 1) >> l) * step_us + scan_us
-        if t < best:
-            best, level = t, l
-    return level
 
 
 def code_hash(path):
@@ -147,9 +128,9 @@ def calibrate_copy(mib):
 
 def sweep(kind, reps=20):
     """Time ts_chain_logpartition (the scan) against ts_chain_logpartition_sequential (the
-    left-to-right forward algorithm) on seeded N(0,1) potentials with full lengths: the
-    depth-versus-work trade-off of the parallel scan (the paper's Fig. 4a and 4c shapes, and
-    long sequences of 128 and 256 labels, where the tree does C times the serial work)."""
+    left-to-right forward algorithm) on seeded N(0,1) potentials with full lengths, on the
+    paper's Fig. 4a and 4c shapes and on long sequences of 128 and 256 labels.  Both do C^2
+    work per edge; tree_flop is what the paper's tree of products would do."""
     import numpy as np
     import torch
 
@@ -192,10 +173,7 @@ def sweep(kind, reps=20):
         ms_scan = timed(lambda: binding.logpartition(pot, out=out, ws=ws))
         ms_seq = timed(lambda: binding.logpartition_sequential(pot, out=out))
         fused = binding.workspace_bytes(binding.OP_LOGPARTITION, B, N, C) == 0
-        D = max(0, (N - 2).bit_length())                     # levels above the N - 1 leaves
-        lscan = node_scan_level(N - 1, D) if 64 < C <= 128 and D >= 2 else 0
-        path = ("single launch" if fused else "chunks" if C <= 64 else
-                f"tree to level {lscan}, recursion over its nodes" if lscan else "multi-launch tree")
+        path = "single launch" if fused else "chunked recursions"
         tree_flop = 2 * B * max(N - 2, 0) * C ** 3           # tree products: 2 C^3 flop each
         serial_flop = 2 * B * (N - 1) * C ** 2              # left to right: 2 C^2 per step
         print(json.dumps({"sweep": kind, "B": B, "N": N, "C": C,
@@ -273,8 +251,8 @@ def ops(w, samples, reps=50):
 
 
 def semi(name, steps, warmup):
-    """Semi-Markov CRF: log Z + segment marginals and the best segmentation per step (the
-    chain scan over K*C expanded states), HIP-event timed like the chain step."""
+    """Semi-Markov CRF: log Z + segment marginals and the best segmentation per step, HIP-event
+    timed like the chain step."""
     import torch
 
     from paper_2002_00876_amd import binding, workloads
@@ -326,7 +304,9 @@ def semi(name, steps, warmup):
         "value": round(B * N / (ms_step * 1e-3), 1), "unit": "tokens/s",
         "ms_per_step": round(ms_step, 5), "steps": steps, "warmup": warmup,
         "config": {"workload": f"{name}: B={B} N={N} K={K} C={C}", "expanded_labels": K * C,
-                   "chain_path": "fused single launch" if fused else "multi-launch tree"},
+                   "chain_path": "fused single launch" if fused else
+                   "walks over the segment potentials, or for long sequences the chunked "
+                   "recursions over the expanded chain"},
         "breakdown": {"marginals_ms": round(ms_marg, 5), "viterbi_ms": round(ms_vit, 5)},
         "paper_context": {"tokens_per_s": 87e3,
                           "note": "Table 1 semi-Markov, K80, B=32 N=25 C=20 K=5; log Z only"},
@@ -420,8 +400,8 @@ def main():
 
     def both_call():
         # the whole hot path in one call: on the single-launch path one launch, where the
-        # marginals and the Viterbi workgroups run side by side; on the multi-launch tree
-        # the Viterbi sequence runs on a side stream beside the marginals sequence
+        # marginals and the Viterbi workgroups run side by side; otherwise the Viterbi
+        # sequence runs on a side stream beside the marginals sequence
         binding.marginals_viterbi(pot, lens, out=(logz, marg, path, score), ws=ws_mv)
 
     step = {"marginals": marg_call, "viterbi": vit_call, "both": both_call}[args.step]
@@ -484,60 +464,27 @@ def main():
     tokens = B * N
     value = tokens / (ms_step * 1e-3)
 
-    # Roofline of the timed call.  On the single-launch path the marginals call is one
-    # kernel (k_small_log); on the multi-launch tree it is a sequence of kernels whose bound
-    # is the call's algorithmic work: read the valid edges and write all marginals (HBM),
-    # and 2 C^3 flop per tree product on the matrix cores (MFMA: fp32, or for C a multiple
-    # of 128 the six-product bf16 split at 2.5 PFLOP/s / 6).  The binding resource is the
-    # one with the longer time at its peak.
+    # Roofline of the timed call: the recursions do a few operations per entry of the edges, so the
+    # bound is HBM: read the valid edges once and write the outputs once.
     fused = binding.workspace_bytes(binding.OP_MARGINALS, B, N, C) == 0
-    bf16x6 = not fused and C > 64 and C % 128 == 0
-    cmp_peak = MFMA_BF16X6_PEAK if bf16x6 else MFMA_F32_PEAK
 
-    def roofline(kind, sec):
-        if kind == "marginals":
-            t_mem, t_cmp = alg["marg_bytes"] / HBM_PEAK, alg["marg_flops"] / cmp_peak
-            if t_mem >= t_cmp:
-                a = alg["marg_bytes"] / sec / 1e9
-                r = {"bound": "hbm", "achieved": round(a, 2), "peak": HBM_PEAK / 1e9,
-                     "unit": "GB/s", "frac": float(f"{a / (HBM_PEAK / 1e9):.4g}")}
-            else:
-                a = alg["marg_flops"] / sec / 1e12
-                r = {"bound": "mfma", "achieved": round(a, 3), "peak": round(cmp_peak / 1e12, 2),
-                     "unit": "TFLOP/s", "frac": float(f"{a / (cmp_peak / 1e12):.4g}"),
-                     "peak_note": ("bf16 dense 2500 TFLOP/s / 6: six bf16 products per float32 "
-                                   "product (three-part split of each operand)" if bf16x6 else
-                                   "fp32 dense MFMA")}
-            r["algorithmic_bytes"] = alg["marg_bytes"]
-            r["algorithmic_flops"] = alg["marg_flops"]
-        else:
-            t_mem, t_cmp = alg["vit_bytes"] / HBM_PEAK, alg["vit_ops"] / VALU_F64_OPS_PEAK
-            if t_mem >= t_cmp:
-                a = alg["vit_bytes"] / sec / 1e9
-                r = {"bound": "hbm", "achieved": round(a, 2), "peak": HBM_PEAK / 1e9,
-                     "unit": "GB/s", "frac": float(f"{a / (HBM_PEAK / 1e9):.4g}")}
-            else:
-                a = alg["vit_ops"] / sec / 1e12
-                r = {"bound": "alu", "achieved": round(a, 3), "peak": VALU_F64_OPS_PEAK / 1e12,
-                     "unit": "T fp64 add/max per s", "frac": float(f"{a / (VALU_F64_OPS_PEAK / 1e12):.4g}")}
-            r["algorithmic_bytes"] = alg["vit_bytes"]
-            r["algorithmic_fp64_ops"] = alg["vit_ops"]
-        r["roofline_ms"] = round(max(t_mem, t_cmp) * 1e3, 6)
-        return r
+    def roofline(nbytes, flops, sec):
+        a = nbytes / sec / 1e9
+        return {"bound": "hbm", "achieved": round(a, 2), "peak": HBM_PEAK / 1e9, "unit": "GB/s",
+                "frac": float(f"{a / (HBM_PEAK / 1e9):.4g}"), "algorithmic_bytes": nbytes,
+                "algorithmic_flops": flops, "roofline_ms": round(nbytes / HBM_PEAK * 1e3, 6)}
 
-    roof = roofline("marginals", ms_marg * 1e-3)
+    roof = roofline(alg["marg_bytes"], alg["marg_flops"], ms_marg * 1e-3)
     dom = "k_small_log" if fused else "ts_chain_marginals"
     roof["traffic"] = measured_traffic(dom, w.name)
-    if fused:
-        roof["kernel"] = dom
-    elif C <= 64:
-        roof["kernel"] = ("ts_chain_marginals (the call's kernel sequence: k_chunk_up, "
-                          "k_chunk_scan, k_chunk_form)")
-    else:
-        roof["kernel"] = ("ts_chain_marginals (the call's kernel sequence: k_leaf_max, "
-                          "k_up_log per level, k_root_log, k_down_log per level, k_form_*)")
+    both_ways = 4 * B * E * C * C <= 320 << 20
+    roof["kernel"] = dom if fused else (
+        "ts_chain_marginals (the call's kernel sequence: " +
+        ("k_rec_log both ways at once, k_rec_form" if both_ways else
+         "k_rec_log forward, then backward with the marginals") +
+        ", and the launches that find no sequence left over)")
     roof["kernel_ms"] = round(ms_marg, 5)
-    roof_v = roofline("viterbi", ms_vit * 1e-3)
+    roof_v = roofline(alg["vit_bytes"], alg["vit_ops"], ms_vit * 1e-3)
 
     out = {
         "metric": "tokens/sec for linear-chain logZ+marginals (B,N,C); % of HBM/compute roofline",
@@ -558,9 +505,7 @@ def main():
                             "viterbi": "ts_chain_viterbi (path and score)",
                             "both": "ts_chain_marginals_viterbi (log Z, marginals, Viterbi)"}[
                                 args.step] + (", replayed as a HIP graph" if args.graph else ""),
-                   "path": ("fused single launch per call" if fused else
-                            "chunks: three launches per call" if C <= 64 else
-                            "multi-launch tree")},
+                   "path": "fused single launch per call" if fused else "chunked recursions"},
         "breakdown": {"marginals_ms": round(ms_marg, 5), "viterbi_ms": round(ms_vit, 5),
                       "marginals_viterbi_ms": round(ms_both, 5),
                       "marginals_tokens_per_s": round(tokens / (ms_marg * 1e-3), 1),
@@ -568,9 +513,8 @@ def main():
                       "whole_path_tokens_per_s": round(tokens / (ms_both * 1e-3), 1),
                       "valid_tokens_per_s": round(float(lens_h.sum()) / (ms_step * 1e-3), 1),
                       "viterbi_roofline": roof_v},
-        "dtype_note": "log semiring in fp32 precision (products on the bf16 matrix cores from "
-                      "three-part bf16 splits of the fp32 operands for 128-wide tiles, fp32 MFMA "
-                      "elsewhere; float64 row/column offsets); Viterbi max-plus in float64",
+        "dtype_note": "log semiring in linear fp32 vectors with integer exponents, log Z's terms "
+                      "in float64; Viterbi scores in float64",
         "paper_context": {"tokens_per_s": PAPER_CONTEXT_TOKENS_PER_S,
                           "note": "Table 1, K80, B=32 N=25 C=20; not the same metric"},
         "roofline": roof,
