@@ -329,7 +329,11 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
             });
             // Walks that never meet are left to one workgroup per sequence, E dependent steps;
             // where the tree would be much faster than that (few and long sequences), it takes
-            // those sequences instead (about 29 T add/max per second, 4 us per launch)
+            // those sequences instead (about 29 T add/max per second, 4 us per launch).  Much:
+            // its launches follow every call, usually to find nothing, and walks that meet late
+            // finish sooner in order.  B = 4, N = 8192, C = 128 (a ratio of 2.2), us without / with
+            // the tree behind: N(0, 1) 582 / 656, transitions that keep a label by 12 2647 / 6728,
+            // two label sets without transitions between them 11672 / 6754.
             const double tree_us = 8.0 * D + 2.0 * (double)B * p->E * C * C * C / 29e6;
             if (p->rec_K > 1 && walk_step_us(C) * p->E > 3 * tree_us)
                 p->gate = bump.take<int32_t>((size_t)B);

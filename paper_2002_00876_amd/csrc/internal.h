@@ -184,6 +184,16 @@ hipError_t launch_marginals_tree(const Plan& p, const float* pot, const int32_t*
                                  float* marg, hipStream_t s);
 hipError_t launch_rec_log(const Plan& p, const float* pot, const int32_t* lengths, float* logZ,
                           float* marg, hipStream_t s);
+// Chunks of S edges that one workgroup walks in order, where the rounds have left some, before it
+// leaves the sequence to the tree: 256 edges' worth and at most a quarter of the K chunks (twice
+// that, counting what changes on the way).  With chunks of 16 or 32 edges usual inputs leave a few
+// (Viterbi of N(0, 1) potentials, B = 1, C = 129, N = 600: 704 us by the tree, 992 by the rounds and
+// the tree, 303 with the chunk walked in order; C = 256, N = 2500: 3486, 3991, 732); chains that never
+// mix leave nearly all, and go to the tree at once.
+inline int rec_limit(int64_t S, int64_t K) {
+    const int64_t n = 256 / S < K / 4 ? 256 / S : K / 4;
+    return n > 1 ? (int)n : 1;
+}
 int rec_threads(int64_t C);   // threads of a workgroup of the recursions
 hipError_t launch_rec_max(const Plan& p, const float* pot, const int32_t* lengths, float* score,
                           hipStream_t s);

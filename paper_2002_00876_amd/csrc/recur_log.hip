@@ -57,6 +57,7 @@ struct RecLogArgs {
     float* logZ;        // [B] or nullptr
     int32_t* gate;      // [B]
     bool tree_pending;  // walks that do not meet are left to the tree, too
+    int limit;          // unless they are at most this many chunks
     bool meet;          // log Z of one chunk: the two directions meet in its middle
     int32_t* xbeg;      // [B, K] exponent of the backward walk
     // log Z once more (k_rec_refine); fine is nullptr where no sequence is long enough
@@ -430,19 +431,23 @@ __device__ void last_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b) {
     const int64_t nbk = a.B * a.K, b0 = (int64_t)b * a.K;
     const int n = (Eb + a.S - 1) / a.S;
     int32_t* const chg = a.chg + (size_t)kRecRounds * nbk + b0;   // this walk's own changes
-    bool pending = false, left = false;
-    for (int k = threadIdx.x; k < n; k += F::kT) {
-        left |= a.bad[b0 + k] != 0;
-        pending |= k > 0 && a.chg[(size_t)(kRecRounds - 1) * nbk + b0 + k - 1] != 0;
-        chg[k] = 0;
+    bool left = false;
+    int pending = 0, walked = 0;
+    for (int k0 = 0; k0 < n; k0 += F::kT) {
+        const int k = k0 + (int)threadIdx.x;
+        left |= k < n && a.bad[b0 + k] != 0;
+        pending += __syncthreads_count(k > 0 && k < n && a.chg[(size_t)(kRecRounds - 1) * nbk + b0 + k - 1] != 0);
+        if (k < n) chg[k] = 0;
     }
-    left = __syncthreads_or(left);
-    pending = __syncthreads_or(pending) && !left;
-    left |= pending && a.tree_pending;
+    left = __syncthreads_or(left) || (a.tree_pending && pending > a.limit);
     bool changed = false;
-    for (int k = 1; pending && !left && k < n; ++k) {
+    for (int k = 1; pending > 0 && !left && k < n; ++k) {
         const bool late = a.chg[(size_t)(kRecRounds - 1) * nbk + b0 + k - 1];
         if (!uniform(changed || late)) continue;
+        if (a.tree_pending && walked++ == 2 * a.limit) {
+            left = true;
+            break;
+        }
         changed = again_fwd<F>(a, sm, b, k, Eb,
                                a.vend + ((size_t)(kRecRounds + changed) * nbk + b0 + k - 1) * a.C,
                                latest_version(a.chg, nbk, b0 + k, kRecRounds), kRecRounds + 1);
@@ -860,19 +865,23 @@ __device__ void last_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b) {
     const int64_t nbk = a.B * a.K, b0 = (int64_t)b * a.K;
     const int n = (Eb + a.S - 1) / a.S;
     int32_t* const chg = a.chgb + (size_t)kRecRounds * nbk + b0;
-    bool pending = false, left = false;
-    for (int k = threadIdx.x; k < n; k += F::kT) {
-        left |= a.badb[b0 + k] != 0 || a.bad[b0 + k] != 0;
-        pending |= k + 1 < n && a.chgb[(size_t)(kRecRounds - 1) * nbk + b0 + k + 1] != 0;
-        chg[k] = 0;
+    bool left = false;
+    int pending = 0, walked = 0;
+    for (int k0 = 0; k0 < n; k0 += F::kT) {
+        const int k = k0 + (int)threadIdx.x;
+        left |= k < n && (a.badb[b0 + k] != 0 || a.bad[b0 + k] != 0);
+        pending += __syncthreads_count(k + 1 < n && a.chgb[(size_t)(kRecRounds - 1) * nbk + b0 + k + 1] != 0);
+        if (k < n) chg[k] = 0;
     }
-    left = __syncthreads_or(left);
-    pending = __syncthreads_or(pending) && !left;
-    left |= pending && a.tree_pending;
+    left = __syncthreads_or(left) || (a.tree_pending && pending > a.limit);
     bool changed = false;
-    for (int k = n - 2; pending && !left && k >= 0; --k) {
+    for (int k = n - 2; pending > 0 && !left && k >= 0; --k) {
         const bool late = a.chgb[(size_t)(kRecRounds - 1) * nbk + b0 + k + 1];
         if (!uniform(changed || late)) continue;
+        if (a.tree_pending && walked++ == 2 * a.limit) {
+            left = true;
+            break;
+        }
         changed = again_bwd<F, kForm>(a, sm, b, k, Eb,
                                       a.vbeg + ((size_t)(kRecRounds + changed) * nbk + b0 + k + 1) * a.C,
                                       latest_version(a.chgb, nbk, b0 + k, kRecRounds), kRecRounds + 1);
@@ -1150,6 +1159,7 @@ hipError_t launch_rec_log(const Plan& p, const float* pot, const int32_t* length
     a.chg = p.rec_chg; a.shift = p.rec_shift; a.ratio = p.rec_ratio; a.last = p.rec_last; a.bad = p.rec_bad;
     a.beta = p.rec_beta; a.vbeg = p.rec_vbeg; a.chgb = p.rec_chgb; a.badb = p.rec_badb;
     a.marg = marg; a.logZ = logZ; a.gate = p.gate; a.gateb = p.rec_gateb; a.tree_pending = p.rec_tree;
+    a.limit = rec_limit(p.rec_S, p.rec_K);
     a.xbeg = p.rec_xbeg; a.epot = p.rec_exp;
     if (logZ && p.E > kRefineEdges) { a.fine = p.rec_fine; a.count = p.rec_count; a.part = p.rec_part; }
     a.meet = !marg && logZ && p.rec_K == 1 && p.E >= 4;

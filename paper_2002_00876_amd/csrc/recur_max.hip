@@ -27,6 +27,7 @@ struct RecMaxArgs {
     int32_t* zlast;     // [B]
     float* score;       // [B]
     int32_t* gate;      // [B] sequences left to the tree, or nullptr: none are
+    int limit;          // chunks walked in order before a sequence is left to the tree
 };
 
 // What two walks' scores of one label may differ by, beyond their offset, of the larger one's
@@ -309,7 +310,8 @@ __global__ __launch_bounds__(F::kT, F::kNW == 16 ? 4 : 2) void k_rec_max_again(R
 }
 
 // One workgroup per sequence: what the rounds have left is walked in order, each chunk from
-// its predecessor's final end scores, or marked for the tree (a.gate); then the last label and
+// its predecessor's final end scores, or marked for the tree where that is more than a few chunks
+// and the tree is faster (a.gate); then the last label and
 // the score.  Usually nothing is left; a sequence whose walks never meet, or whose scores pass
 // kMaxScore (masks that no path avoids), is walked whole here.
 template <class F>
@@ -323,15 +325,18 @@ __global__ __launch_bounds__(F::kT, F::kNW == 16 ? 4 : 2) void k_rec_max_finish(
     }
     const int64_t nbk = a.B * a.K;
     const int n = (Eb + a.S - 1) / a.S;
-    bool changed = false, pending = false;
-    for (int k = 1 + threadIdx.x; k < n; k += F::kT)
-        pending |= a.chg[(size_t)(kRecRounds - 1) * nbk + (int64_t)b * a.K + k - 1] != 0;
-    pending = __syncthreads_or(pending);
-    for (int k = 1; pending && k < n; ++k) {
+    bool changed = false;
+    int pending = 0, walked = 0;
+    for (int k0 = 1; k0 < n; k0 += F::kT) {
+        const int k = k0 + (int)threadIdx.x;
+        pending += __syncthreads_count(k < n && a.chg[(size_t)(kRecRounds - 1) * nbk + (int64_t)b * a.K + k - 1] != 0);
+    }
+    for (int k = 1; pending > 0 && k < n; ++k) {
         const int64_t bk = (int64_t)b * a.K + k;
         const bool late = a.chg[(size_t)(kRecRounds - 1) * nbk + bk - 1];
         if (!uniform(changed || late)) continue;
-        if (a.gate) {   // (the tree writes the last label and the score, too)
+        // (the tree writes the last label and the score, too)
+        if (a.gate && (pending > a.limit || walked++ == 2 * a.limit)) {
             if (threadIdx.x == 0) a.gate[b] = 1;
             return;
         }
@@ -408,6 +413,7 @@ hipError_t launch_rec_max(const Plan& p, const float* pot, const int32_t* length
     a.S = (int)p.rec_S; a.K = (int)p.rec_K;
     a.delta = p.rec_delta; a.vend = p.rec_vendd; a.chg = p.rec_chg; a.shift = p.rec_shift;
     a.last = p.rec_last; a.bp = p.bp; a.zlast = p.zlast; a.score = score; a.gate = p.gate;
+    a.limit = rec_limit(p.rec_S, p.rec_K);
     return with_rec_cfg(p.C, [&](auto f) { return launch<decltype(f)>(a, s); });
 }
 

@@ -140,6 +140,14 @@ def test_outside_the_linear_range(C):
     check_all(pot, lens, f"range C={C}")
 
 
+@pytest.mark.parametrize("C,N", [(129, 600), (160, 1000), (200, 600), (256, 300), (256, 600)])
+def test_some_walks_left_after_the_rounds(C, N):
+    # short chunks (32 edges for Viterbi, 16 for the marginals): some do not meet in two rounds and are
+    # walked in order before the tree is asked, at the first edges, later ones and the last
+    pot, lens = W.random_case(39800 + C + N, 2, N, C, lengths=[N, N - 77])
+    check_all(pot, lens, f"walked in order C={C} N={N}")
+
+
 @pytest.mark.parametrize("C", [9, 24, 36, 64, 75, 100, 130, 256])
 def test_range_left_by_a_second_walk(C):
     # two label sets without transitions between them, one falling behind by e^-0.3 per edge: every
