@@ -208,9 +208,9 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
             p->rec_shift = m.take<double>(nbk);
             p->rec_ratio = m.take<double>(nbk);
             p->rec_last = m.take<int32_t>(nbk);
-            p->rec_bad = m.take<int32_t>(nbk);
+            p->rec_bad = m.take<int32_t>(2 * nbk);
             p->rec_vbeg = m.take<float>(versions * nbk * C);
-            p->rec_badb = m.take<int32_t>(nbk);
+            p->rec_badb = m.take<int32_t>(2 * nbk);
             p->rec_gateb = m.take<int32_t>((size_t)B);
             p->rec_xbeg = m.take<int32_t>(nbk);
             p->rec_fine = m.take<int32_t>((size_t)B);

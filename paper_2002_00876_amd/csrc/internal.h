@@ -91,11 +91,11 @@ struct Plan {
     int32_t* rec_cx = nullptr;     // [B, E]
     float* rec_vend = nullptr;     // [kRecRounds + 2][B, K, C]
     int32_t* rec_xend = nullptr;   // [kRecRounds + 2][B, K]
-    int32_t* rec_bad = nullptr;    // [B, K] the chunk has left the walks' range
+    int32_t* rec_bad = nullptr;    // [2][B, K] the chunk has left the walks' range
     float* rec_beta = nullptr;     // [B, E, C]
     float* rec_vbeg = nullptr;     // [kRecRounds + 2][B, K, C]
     int32_t* rec_chgb = nullptr;   // [kRecRounds + 1][B, K]
-    int32_t* rec_badb = nullptr;   // [B, K]
+    int32_t* rec_badb = nullptr;   // [2][B, K]
     int32_t* rec_gateb = nullptr;  // [B]
     int32_t* rec_xbeg = nullptr;   // [B, K]
     int32_t* rec_fine = nullptr;   // [B] log Z is refined (recur_log.hip)

@@ -46,12 +46,12 @@ struct RecLogArgs {
     double* shift;      // [B, K] what the exponents past `last` lack, to float's precision
     double* ratio;      // [B, K] the ratio whose log2 shift holds
     int32_t* last;      // [B, K] last position that the chunk's latest walk has rewritten
-    int32_t* bad;       // [B, K] the chunk has left the range
+    int32_t* bad;       // [2][B, K] the chunk has left the range: its first walk, a later one
     // backward
     float* beta;        // [B, E, C] b before each edge (inside chunks)
     float* vbeg;        // [kRecRounds + 2][B, K, C] b before the chunk's first edge
     int32_t* chgb;      // [kRecRounds + 1][B, K]
-    int32_t* badb;      // [B, K]
+    int32_t* badb;      // [2][B, K]
     int32_t* gateb;     // [B] what the backward walks beside the forward ones leave to the tree
     float* marg;
     float* logZ;        // [B] or nullptr
@@ -322,7 +322,7 @@ __device__ void finish_fwd(const RecLogArgs& a, int64_t b, int n, const float* v
                                    : latest_version(a.chg, nbk, bk, kRecRounds + 1);
         const double ratio = a.ratio[bk];
         sum += a.xend[(size_t)ver * nbk + bk] + (a.shift[bk] - (double)__builtin_amdgcn_logf((float)ratio)) + log2(ratio);
-        left |= a.bad[bk] != 0;
+        left |= (a.bad[bk] | a.bad[nbk + bk]) != 0;
     }
     for (int i = lane; i < a.C; i += 64) tot += v[i];
     sum = wave_sum_d(sum);
@@ -367,6 +367,7 @@ __device__ void first_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k) {
         a.ratio[bk] = 1.0;
         a.last[bk] = s;
         a.bad[bk] = bad;
+        a.bad[a.B * a.K + bk] = 0;
     }
     if (a.K > 1 || a.meet) return;
     __syncthreads();
@@ -399,7 +400,7 @@ __device__ bool again_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k, int 
         // exponents past `last` are an older walk's; none are once the whole chunk has been
         // walked again
         a.last[bk] = r.last;
-        if (bad) a.bad[bk] = 1;
+        if (bad) a.bad[nbk + bk] = 1;
     }
     return !r.agreed;
 }
@@ -413,10 +414,8 @@ __device__ void round_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b, int k) {
     const int64_t nbk = a.B * a.K, bk = (int64_t)b * a.K + k;
     const int ver = a.round - 1;   // the predecessor's version, if it is new
     bool changed = false;
-    // (the predecessor's workgroup may be marking its chunk now: one answer for all waves here.  The
-    // sequence is left to the tree whichever it is.)
-    if (k > 0 && (ver == 0 || a.chg[(size_t)(ver - 1) * nbk + bk - 1]) &&
-        !__syncthreads_or(a.bad[bk] | a.bad[bk - 1]))
+    // (the first walks' marks: the predecessor's workgroup may be marking a later one now)
+    if (k > 0 && (ver == 0 || a.chg[(size_t)(ver - 1) * nbk + bk - 1]) && !(a.bad[bk] | a.bad[bk - 1]))
         changed = again_fwd<F>(a, sm, b, k, Eb, a.vend + ((size_t)ver * nbk + bk - 1) * a.C,
                                latest_version(a.chg, nbk, bk, ver), a.round);
     if (threadIdx.x == 0) a.chg[(size_t)ver * nbk + bk] = changed;
@@ -435,7 +434,7 @@ __device__ void last_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b) {
     int pending = 0, walked = 0;
     for (int k0 = 0; k0 < n; k0 += F::kT) {
         const int k = k0 + (int)threadIdx.x;
-        left |= k < n && a.bad[b0 + k] != 0;
+        left |= k < n && (a.bad[b0 + k] | a.bad[nbk + b0 + k]) != 0;
         pending += __syncthreads_count(k > 0 && k < n && a.chg[(size_t)(kRecRounds - 1) * nbk + b0 + k - 1] != 0);
         if (k < n) chg[k] = 0;
     }
@@ -819,6 +818,7 @@ __device__ void first_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k) {
     bad = __syncthreads_or(bad);
     if (threadIdx.x == 0) {
         a.badb[bk] = bad;
+        a.badb[a.B * a.K + bk] = 0;
         a.xbeg[bk] = x;
         if (a.K == 1) (kForm ? a.gate : a.gateb)[b] = bad;
     }
@@ -839,7 +839,7 @@ __device__ bool again_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k, int 
             : walk_bwd<F, true, kForm, false>(a, sm, b, k, s, e, x, bad, old_beg);
     if (!agreed) end_bwd<F>(a, sm, s, bk, ver);
     bad = __syncthreads_or(bad);
-    if (bad && threadIdx.x == 0) a.badb[bk] = 1;
+    if (bad && threadIdx.x == 0) a.badb[nbk + bk] = 1;
     return !agreed;
 }
 
@@ -852,7 +852,7 @@ __device__ void round_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b, int k) {
     const int ver = a.round - 1;
     bool changed = false;
     if ((k + 1) * a.S < Eb && (ver == 0 || a.chgb[(size_t)(ver - 1) * nbk + bk + 1]) &&
-        (kForm || !__syncthreads_or(a.badb[bk] | a.badb[bk + 1])))   // (as going forward)
+        (kForm || !(a.badb[bk] | a.badb[bk + 1])))
         changed = again_bwd<F, kForm>(a, sm, b, k, Eb, a.vbeg + ((size_t)ver * nbk + bk + 1) * a.C,
                                       latest_version(a.chgb, nbk, bk, ver), a.round);
     if (threadIdx.x == 0) a.chgb[(size_t)ver * nbk + bk] = changed;
@@ -869,7 +869,7 @@ __device__ void last_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b) {
     int pending = 0, walked = 0;
     for (int k0 = 0; k0 < n; k0 += F::kT) {
         const int k = k0 + (int)threadIdx.x;
-        left |= k < n && (a.badb[b0 + k] != 0 || a.bad[b0 + k] != 0);
+        left |= k < n && (a.badb[b0 + k] | a.badb[nbk + b0 + k] | a.bad[b0 + k]) != 0;
         pending += __syncthreads_count(k + 1 < n && a.chgb[(size_t)(kRecRounds - 1) * nbk + b0 + k + 1] != 0);
         if (k < n) chg[k] = 0;
     }
@@ -888,7 +888,7 @@ __device__ void last_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b) {
         changed = uniform(changed);
         if (threadIdx.x == 0) chg[k] = changed;
         __syncthreads();
-        left |= uniform(a.badb[b0 + k] != 0);
+        left |= uniform(a.badb[nbk + b0 + k] != 0);
     }
     if (threadIdx.x == 0) (kForm ? a.gate : a.gateb)[b] = left;
 }
