@@ -181,9 +181,11 @@ __device__ __forceinline__ void tile_load_row(float (&x)[F::kCB], __amdgpu_buffe
 // Chunk k of sequence b of a recursion: its edges [s, e), and the versions of end vectors.
 // Round r's walks write version r; chg[r][b][k] (r >= 1) says that they did.
 __device__ __forceinline__ int latest_version(const int32_t* chg, int64_t nbk, int64_t bk, int r) {
-    for (int q = r; q >= 1; --q)
-        if (chg[(size_t)(q - 1) * nbk + bk]) return q;
-    return 0;
+    int v = 0;   // (all at once: a walk usually has changed nothing since version 0)
+#pragma unroll
+    for (int q = 1; q <= kRecRounds + 1; ++q)
+        if (q <= r && chg[(size_t)(q - 1) * nbk + bk]) v = q;
+    return v;
 }
 
 // Calls fn(cfg) with the layout for C labels: 16-byte loads when rows are 16-byte aligned
