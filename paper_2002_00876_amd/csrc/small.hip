@@ -773,6 +773,11 @@ __device__ __forceinline__ void small_log_body(const SmallLogArgs& a, const int6
 // N = 100, C = 8: 33.3 / 21.1, 16.9 / 18.2, 21.8 / 24.8.  So marginals always walk, and log Z
 // and Viterbi up to kWalkEdges edges (only up to 8 labels fit LDS past that).
 constexpr int kWalkEdges = 80;
+// Up to 4 labels the Viterbi tree is cheaper, and past 64 edges it has a level more (B = 256, C = 3,
+// tree / walk: 55 edges 15.5 / 15.3, 63 15.7 / 16.6, 71 19.4 / 18.7, 79 19.4 / 19.8).
+__device__ __forceinline__ bool max_walks(int C, int Eb) {
+    return C > 4 ? Eb <= kWalkEdges : Eb <= 56 || (Eb > 64 && Eb <= 76);
+}
 //
 // A vector's entry j sits in lane j of each group of kW lanes; group g of the kGroups sums the
 // rows g * kH .. g * kH + kH - 1 (columns for the backward walk).
@@ -1312,7 +1317,7 @@ __device__ __forceinline__ void small_max_body(const SmallMaxArgs& a, const int6
     MaxLayout ly;
     ly.init(C, Eb, nodes);
     // ---- leaves (fp32, flat), and for the tree its levels and node table
-    const bool tree = Eb > kWalkEdges;
+    const bool tree = !max_walks(C, Eb);
     if (tree) {
         if (w == kSmallWaves - 1) tree_init_wave(T, Eb);
         build_node_table(Eb, nodes, ly.info);

@@ -35,3 +35,12 @@ def test_outside_the_range(C):
     pot[2, 3:7, :, 1:2] -= 20.0
     pot[3, 2, : C // 2] = -np.inf
     check_all(pot, lens, f"range C={C}")
+
+
+@pytest.mark.parametrize("C", [1, 2, 4])
+def test_viterbi_walk_and_tree_lengths_of_few_labels(C):
+    # 56 / 57, 64 / 65 and 76 / 77 edges, where Viterbi of up to 4 labels changes between them
+    lens = [57, 58, 65, 66, 77, 78, 79, 1]
+    for kind, kw in (("normal", {}), ("int", dict(int_range=1))):
+        pot, ln = W.random_case(45000 + C, 8, 79, C, kind=kind, lengths=lens, **kw)
+        check_all(pot, ln, f"few labels C={C} {kind}")
