@@ -3,6 +3,7 @@
 // kernels (tree_log.hip, tree_max.hip, small.hip); this file only checks and enqueues.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <cmath>
 #include <cstring>
@@ -149,6 +150,31 @@ void recur_chunks(int op, int64_t B, int64_t E, int64_t C, int64_t* S, int64_t* 
     *K = (E + *S - 1) / *S;
 }
 
+// Whether the chunk kernels (C <= 64) compute log Z or the marginals of short chains alone, without
+// the recursions before them: what the recursions save must pay for their launches.  Estimated
+// times in us, with S = 2^lc edges per chunk and n chunks: 2 S for the products (more past one
+// workgroup per compute unit), 0.95 per chunk of the scan, both more where rows are not 16-byte
+// aligned; 0.318 per edge for log Z of one chunk by both directions, 0.6 per edge of several chunks.  Measured (log Z, us, chunk kernels / recursions, B =
+// 4, C = 40; C = 33 in brackets): N = 2: 7.0 / 8.7, 8: 12.8 / 15.5, 20: 17.0 / 16.7, 64: 28.2 / 29.9
+// (31.7 / 30.8), 140: 37.7 / 54.8 (42.4 / 56.0), 200: 44.4 / 48.0 (49.7 / 49.9), 300: 53.7 / 49.3; B =
+// 64: N = 8: 13.7 / 15.9, 64: 40.3 / 31.2.  Marginals: N = 2: 10.1 / 16.2, 3: 16.5 / 18.7 (18.5 / 18.9),
+// 4: 21.0 / 18.5; B = 1024, N = 3: 36.4 / 27.4.
+bool chunk_alone(const Plan& p) {
+    if (p.C <= 32) return false;
+    const double n = (double)((p.E + ((int64_t)1 << p.lc) - 1) >> p.lc);
+    if (p.op == TS_OP_MARGINALS) return p.E == 1 || (p.E == 2 && p.C % 4 == 0 && p.B <= 128);
+    const double fill = (double)p.B * n / 256.0;
+    const double more = fill > 1.0 ? 1.0 + 1.4 * (fill - 1.0) : 1.0;
+    double chunk = 2.0 * (double)(1 << p.lc) * more + 0.95 * n + 4.0;
+    if (p.C % 4 != 0) chunk *= 1.13 + 0.01 * (double)(p.C - 33);
+    if (p.E == 1) chunk = 7.0;   // (no products)
+    double rec;
+    if (p.E < 4) rec = p.E == 1 ? 8.7 : 11.2;
+    else if (p.rec_K > 1) rec = 0.6 * (double)p.rec_S + 28.0;
+    else rec = std::max(15.3, 10.6 + 0.318 * (double)p.E);
+    return 1.08 * chunk < rec;   // (close calls, which are a matter of the inputs, to the recursions)
+}
+
 bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, bool masks,
                bool recursions) {
     *p = Plan{};
@@ -263,6 +289,10 @@ bool make_plan(int op, int64_t B, int64_t N, int64_t C, void* base, Plan* p, boo
                 const size_t nv = lc > 0 ? n : (size_t)B * p->E;
                 p->u[lc] = bump.take<float>(nv * C);
                 p->v[lc] = bump.take<float>(nv * C);
+            }
+            if (recur && chunk_alone(*p)) {
+                recur = false;
+                p->rec_S = p->rec_K = 0;
             }
             // (the chunk kernels sustain about 40 TFLOP/s of products)
             if (recur) place_log(bump.off, 30.0 + 2.0 * (double)B * p->E * C * C * C / 40e6);

@@ -54,10 +54,11 @@ def test_recursions_stay_within_a_launch(L, monkeypatch, op, C):
     ws = binding.workspace_bytes
     threads = 512 if C < 64 else 1024
     B = (1 << 32) // threads // (1 if op == 2 else 2)
-    with_recursions, without = ws(op, B - 1, 2, C), ws(op, B, 2, C)
+    N = 2 if op == 2 else 8
+    with_recursions, without = ws(op, B - 1, N, C), ws(op, B, N, C)
     monkeypatch.setenv("TS_PATH", "tree")
-    assert with_recursions != ws(op, B - 1, 2, C)
-    assert without == ws(op, B, 2, C)
+    assert with_recursions != ws(op, B - 1, N, C)
+    assert without == ws(op, B, N, C)
 
 
 def test_workspace_sizes(L, monkeypatch):

@@ -140,6 +140,15 @@ def test_outside_the_linear_range(C):
     check_all(pot, lens, f"range C={C}")
 
 
+@pytest.mark.parametrize("C", [33, 40, 63, 64])
+@pytest.mark.parametrize("N", [2, 3, 4, 5, 12, 17, 65, 100, 140, 200])
+def test_short_chains_at_the_chunk_kernels(C, N):
+    # on both sides of the line up to which the chunk kernels compute alone
+    pot, lens = W.random_case(39900 + C + N, 3, N, C, lengths=[N, max(1, N // 2), 1])
+    pot[0, N // 2 - 1, 0, 1:] = -np.inf
+    check_all(pot, lens, f"short C={C} N={N}")
+
+
 @pytest.mark.parametrize("C,N", [(129, 600), (160, 1000), (200, 600), (256, 300), (256, 600)])
 def test_some_walks_left_after_the_rounds(C, N):
     # short chunks (32 edges for Viterbi, 16 for the marginals): some do not meet in two rounds and are
