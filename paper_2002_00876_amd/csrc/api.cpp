@@ -518,6 +518,17 @@ bool semi_walks(int op, int64_t B, int64_t N, int64_t K, int64_t C, const Plan& 
     return semi_walk_bytes(B, N, KC, nullptr, &w) <= ws_bytes;
 }
 
+// Whether the expanded chain of a semi-Markov call takes the vector recursions.  Backward, the state of
+// a segment that still runs r steps holds what the chain gains from there on, so one vector spans the
+// growth of K - 1 steps: with unit normal scores 1 + 1.65 C per step at most (the root x of
+// sum_k C e^(1/2) x^-k = 1).  Past the walks' 2^46 every sequence is left to the tree after all.
+// Measured (marginals, us, tree / recursions and tree): K = 12, C = 20, B = 1, N = 200: 721 / 839; K =
+// 64, C = 1, B = 16, N = 200: 356 / 426; K = 32, C = 8, B = 1, N = 2000: 2766 / 3840; below: K = 16, C = 2,
+// B = 16, N = 200: 248 / 119.
+bool semi_recursions(int op, int64_t K, int64_t C) {
+    return op != TS_OP_MARGINALS || (double)(K - 1) * std::log2(1.0 + 1.65 * (double)C) <= 46.0;
+}
+
 // Sizes only; returns the reason when the dimensions are out of range, else nullptr.
 const char* plan_semi(int op, int64_t B, int64_t N, int64_t K, int64_t C, SemiPlan* q) {
     if (B < 1 || N < 1 || K < 1 || C < 1) return "B, N, K and C must all be >= 1";
@@ -530,7 +541,7 @@ const char* plan_semi(int op, int64_t B, int64_t N, int64_t K, int64_t C, SemiPl
     if (N == 1) return nullptr;   // one token per sequence: no edges, no workspace
     // finiteness masks only where the expansion has structural zeros (K > 1); with K = 1 the
     // expanded chain is the chain itself and takes the same kernels
-    if (!make_plan(op, B, N, q->KC, nullptr, &q->base, /*masks=*/K > 1))
+    if (!make_plan(op, B, N, q->KC, nullptr, &q->base, /*masks=*/K > 1, semi_recursions(op, K, C)))
         return "problem size overflows the supported range";
     const size_t x = align_up(sizeof(float) * B * (N - 1) * q->KC * q->KC);
     q->xpot = 0;
@@ -837,7 +848,8 @@ ts_status ts_semimarkov_marginals(const float* sp, const int32_t* lengths, int64
         if (q.base.fused) {
             e = launch_small_log(xp, lengths, B, N, q.KC, logZ, xm, s);
         } else {
-            make_plan(TS_OP_MARGINALS, B, N, q.KC, w + q.chain, &q.base, K > 1);
+            make_plan(TS_OP_MARGINALS, B, N, q.KC, w + q.chain, &q.base, K > 1,
+                      semi_recursions(TS_OP_MARGINALS, K, C));
             e = log_call(q.base, xp, lengths, logZ, xm, s);
         }
     }

@@ -93,3 +93,10 @@ def test_longest_viterbi_walk(N):
     # 80 steps of 256 states are the most backpointers kept in LDS
     sp, _ = W.semi_case(700 + N, 24, N, 8, 32)
     _check(sp, np.arange(N, N - 24, -1).astype(np.int32), f"N={N}")
+
+
+@pytest.mark.parametrize("K,C,N", [(9, 20, 300), (10, 20, 300), (12, 20, 200), (64, 1, 400)])
+def test_long_segments(K, C, N):
+    # the expanded chain with and without recursions before the tree
+    sp, _ = W.semi_case(900 + K, 2, N, K, C)
+    _check(sp, np.array([N, N - 41], np.int32), f"long segments K={K}")
