@@ -1,6 +1,7 @@
 // api.cpp -- the C ABI declared in include/ts_chain.h: argument validation, workspace
 // planning and the kernel sequence of each call.  All arithmetic happens in the HIP
-// kernels (tree_log.hip, tree_max.hip, small.hip); this file only checks and enqueues.
+// kernels (recur_log.hip, recur_max.hip, small.hip, chunk.hip, tree_log.hip, tree_max.hip,
+// semi_walk.hip); this file only checks, plans and enqueues.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -10,8 +10,9 @@
 // So in further rounds a chunk is walked again from its predecessor's end vector, but only
 // until its vector agrees with the stored one.  A round that reaches its chunk's end without
 // agreeing changes the end vector, and the next chunk is walked again in the next round.
-// After kRounds such rounds a sequence with a change still pending is left to the tree
-// (Plan::gate), which needs no such property.  A sequence of one chunk is exact at once.
+// After kRecRounds such rounds what is still pending is walked in order, or, where that is more than
+// a few chunks and the tree is faster, left to it (Plan::gate), as the tree needs no such property.
+// A sequence of one chunk is exact at once.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -9,8 +9,8 @@
 // n_t = sum_ij a_t E_t b_{t+1} = 2^(c_{t+1} - c_t) a_{t+1} . b_{t+1} is known before the edge
 // is read.
 //
-// The range this needs is checked, not assumed.  While every finite potential is at most
-// kRecMaxPot in magnitude and no entry that is not 0 falls below kRecLow (of a vector scaled
+// The range this needs is checked, not assumed.  While every finite potential is at most 24
+// (kRecPotBits) in magnitude and no entry that is not 0 falls below kRecLow (of a vector scaled
 // by the power of two of the one before it), no product and no sum underflows or overflows:
 // a 0 is then exactly a -inf log message.  A sequence that leaves this range is left to the
 // tree, as is one whose walks do not meet where the tree is much faster than walking it in
@@ -430,18 +430,24 @@ __device__ void last_fwd(const RecLogArgs& a, FwdLds<F>& sm, int b) {
     const int64_t nbk = a.B * a.K, b0 = (int64_t)b * a.K;
     const int n = (Eb + a.S - 1) / a.S;
     int32_t* const chg = a.chg + (size_t)kRecRounds * nbk + b0;   // this walk's own changes
-    bool left = false;
-    int pending = 0, walked = 0;
-    for (int k0 = 0; k0 < n; k0 += F::kT) {
-        const int k = k0 + (int)threadIdx.x;
-        left |= k < n && (a.bad[b0 + k] | a.bad[nbk + b0 + k]) != 0;
-        pending += __syncthreads_count(k > 0 && k < n && a.chg[(size_t)(kRecRounds - 1) * nbk + b0 + k - 1] != 0);
-        if (k < n) chg[k] = 0;
+    bool left = false, any = false;
+    auto late_at = [&](int k) { return k > 0 && a.chg[(size_t)(kRecRounds - 1) * nbk + b0 + k - 1] != 0; };
+    for (int k = threadIdx.x; k < n; k += F::kT) {
+        left |= (a.bad[b0 + k] | a.bad[nbk + b0 + k]) != 0;
+        any |= late_at(k);
+        chg[k] = 0;
     }
-    left = __syncthreads_or(left) || (a.tree_pending && pending > a.limit);
+    int pending = 0, walked = 0;
+    if (__syncthreads_or(left || any)) {   // (rarely)
+        for (int k0 = 0; k0 < n; k0 += F::kT) {
+            const int k = k0 + (int)threadIdx.x;
+            pending += __syncthreads_count(k < n && late_at(k));
+        }
+        left = __syncthreads_or(left) || (a.tree_pending && pending > a.limit);
+    }
     bool changed = false;
     for (int k = 1; pending > 0 && !left && k < n; ++k) {
-        const bool late = a.chg[(size_t)(kRecRounds - 1) * nbk + b0 + k - 1];
+        const bool late = late_at(k);
         if (!uniform(changed || late)) continue;
         if (a.tree_pending && walked++ == 2 * a.limit) {
             left = true;
@@ -865,18 +871,21 @@ __device__ void last_bwd(const RecLogArgs& a, BwdLds<F>& sm, int b) {
     const int64_t nbk = a.B * a.K, b0 = (int64_t)b * a.K;
     const int n = (Eb + a.S - 1) / a.S;
     int32_t* const chg = a.chgb + (size_t)kRecRounds * nbk + b0;
-    bool left = false;
-    int pending = 0, walked = 0;
-    for (int k0 = 0; k0 < n; k0 += F::kT) {
-        const int k = k0 + (int)threadIdx.x;
-        left |= k < n && (a.badb[b0 + k] | a.badb[nbk + b0 + k] | a.bad[b0 + k]) != 0;
-        pending += __syncthreads_count(k + 1 < n && a.chgb[(size_t)(kRecRounds - 1) * nbk + b0 + k + 1] != 0);
-        if (k < n) chg[k] = 0;
+    bool left = false, any = false;
+    auto late_at = [&](int k) { return k + 1 < n && a.chgb[(size_t)(kRecRounds - 1) * nbk + b0 + k + 1] != 0; };
+    for (int k = threadIdx.x; k < n; k += F::kT) {
+        left |= (a.badb[b0 + k] | a.badb[nbk + b0 + k] | a.bad[b0 + k]) != 0;
+        any |= late_at(k);
+        chg[k] = 0;
     }
-    left = __syncthreads_or(left) || (a.tree_pending && pending > a.limit);
+    int pending = 0, walked = 0;
+    if (__syncthreads_or(left || any)) {
+        for (int k0 = 0; k0 < n; k0 += F::kT) pending += __syncthreads_count(late_at(k0 + (int)threadIdx.x));
+        left = __syncthreads_or(left) || (a.tree_pending && pending > a.limit);
+    }
     bool changed = false;
     for (int k = n - 2; pending > 0 && !left && k >= 0; --k) {
-        const bool late = a.chgb[(size_t)(kRecRounds - 1) * nbk + b0 + k + 1];
+        const bool late = late_at(k);
         if (!uniform(changed || late)) continue;
         if (a.tree_pending && walked++ == 2 * a.limit) {
             left = true;

@@ -325,15 +325,17 @@ __global__ __launch_bounds__(F::kT, F::kNW == 16 ? 4 : 2) void k_rec_max_finish(
     }
     const int64_t nbk = a.B * a.K;
     const int n = (Eb + a.S - 1) / a.S;
-    bool changed = false;
+    bool changed = false, any = false;
     int pending = 0, walked = 0;
-    for (int k0 = 1; k0 < n; k0 += F::kT) {
-        const int k = k0 + (int)threadIdx.x;
-        pending += __syncthreads_count(k < n && a.chg[(size_t)(kRecRounds - 1) * nbk + (int64_t)b * a.K + k - 1] != 0);
-    }
+    auto late_at = [&](int k) {
+        return k < n && a.chg[(size_t)(kRecRounds - 1) * nbk + (int64_t)b * a.K + k - 1] != 0;
+    };
+    for (int k = 1 + threadIdx.x; k < n; k += F::kT) any |= late_at(k);
+    if (__syncthreads_or(any))   // (rarely)
+        for (int k0 = 1; k0 < n; k0 += F::kT) pending += __syncthreads_count(late_at(k0 + (int)threadIdx.x));
     for (int k = 1; pending > 0 && k < n; ++k) {
         const int64_t bk = (int64_t)b * a.K + k;
-        const bool late = a.chg[(size_t)(kRecRounds - 1) * nbk + bk - 1];
+        const bool late = late_at(k);
         if (!uniform(changed || late)) continue;
         // (the tree writes the last label and the score, too)
         if (a.gate && (pending > a.limit || walked++ == 2 * a.limit)) {
