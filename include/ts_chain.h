@@ -6,9 +6,11 @@
  *   - the edge marginals p(z_t = i, z_{t+1} = j) = dA/dl[t,i,j]          (Sec. 5.1),
  *   - the max score A*(l) and its argmax label sequence (Viterbi)        (Sec. 5.1-5.2,
  *     Table 2 "Max" semiring),
- * each as a balanced tree of C x C semiring matrix products over the edges of every
- * sequence, padded with the semiring identity (Sec. 6a, Fig. 3).  All arithmetic runs in
- * HIP kernels on the device; the host only validates arguments and enqueues work.
+ * by vector recursions over chunks of every sequence that are all walked at once (Sec. 5.2's
+ * algorithm, C^2 work per edge), and, for the sequences that these leave, by a balanced tree of
+ * C x C semiring matrix products over the edges, padded with the semiring identity (Sec. 6a,
+ * Fig. 3).  All arithmetic runs in HIP kernels on the device; the host only validates arguments
+ * and enqueues work.
  *
  * Common arguments
  *   pot      device pointer, float32 [B, N-1, C, C], row-major and contiguous:
@@ -18,8 +20,8 @@
  *            May be NULL only when N == 1 (no edges).
  *   lengths  device pointer, int32 [B]: number of tokens of each sequence,
  *            1 <= lengths[b] <= N.  Edges t >= lengths[b]-1 are padding: they act as the
- *            identity and their values never affect any result (the multi-launch tree
- *            never reads them; the single-launch kernels for small label sets load whole
+ *            identity and their values never affect any result (the multi-launch kernels
+ *            never read them; the single-launch kernels for small label sets load whole
  *            sequences and discard them).  NULL means every length is N.  Values are not
  *            read on the host: out-of-range values are clamped to [1, N] by the kernels,
  *            unless the environment variable TS_CHECK=1 is set, in which case the call
@@ -83,8 +85,7 @@ int ts_chain_max_labels(void);
 size_t ts_chain_workspace_bytes(int op, int64_t B, int64_t N, int64_t C);
 
 /*
- * Log-partition (Sec. 5.1 A(l); Sec. 5.2 forward algorithm, evaluated as the tree of
- * log-semiring (logsumexp, +) matrix products of Sec. 6a).
+ * Log-partition (Sec. 5.1 A(l); Sec. 5.2 forward algorithm).
  *   logZ  device float32 [B]: log Z of each sequence.  A sequence of one token has no
  *         edges and log Z = log C (its label is free: no start or end potentials).
  *         log Z = -inf when no label sequence has a finite score.
@@ -94,8 +95,8 @@ ts_status ts_chain_logpartition(const float* pot, const int32_t* lengths, int64_
                                 void* stream);
 
 /*
- * Edge marginals, the gradient of A (Sec. 5.1: p(z_p = 1) = dA/dl_p), computed by the
- * outside (down) sweep of the same tree followed by a per-edge local normaliser.
+ * Edge marginals, the gradient of A (Sec. 5.1: p(z_p = 1) = dA/dl_p), from the forward and
+ * backward vectors of every edge with a per-edge local normaliser.
  *   logZ  device float32 [B] or NULL: as for ts_chain_logpartition.
  *   marg  device float32 [B, N-1, C, C], same layout as pot: p(z_t=i, z_{t+1}=j).
  *         Padding edges are written as exactly 0; every entry of a sequence whose
@@ -106,7 +107,7 @@ ts_status ts_chain_marginals(const float* pot, const int32_t* lengths, int64_t B
                              void* stream);
 
 /*
- * Viterbi: the (max, +) instance of the same tree (Sec. 5.1 A*; Sec. 5.2; Table 2 "Max"),
+ * Viterbi: the (max, +) instance of the same recursion (Sec. 5.1 A*; Sec. 5.2; Table 2 "Max"),
  * with float64 accumulation, followed by a lowest-index backtrace.
  *   path  device int32 [B, N]: the argmax label sequence; path[b*N + n] = -1 for
  *         n >= lengths[b].  Ties are broken by the lowest label index at each backtrace
@@ -197,8 +198,9 @@ ts_status ts_chain_logpartition_sequential(const float* pot, const int32_t* leng
  *            segment labelled i.  Entries with t + k > L-1 are never used.
  *   K        maximum segment length, K >= 1 and K * C <= ts_chain_max_labels().
  *   lengths, B, N, C, ws, stream as above; ws is sized by ts_semimarkov_workspace_bytes.
- * The call runs the linear-chain scan over K*C expanded states (the label of the segment
- * in progress and the steps it has left), whose edges it builds in the workspace.
+ * Short calls walk the segment potentials themselves; the others run the linear chain over K*C
+ * expanded states (the label of the segment in progress and the steps it has left), whose edges
+ * they build in the workspace.
  * With K = 1 every result equals the linear chain's on sp[:, :, 0].
  */
 size_t ts_semimarkov_workspace_bytes(int op /* TS_OP_LOGPARTITION, _MARGINALS or _VITERBI */,
@@ -232,13 +234,15 @@ ts_status ts_semimarkov_viterbi(const float* sp, const int32_t* lengths, int64_t
  * ts_chain_marginals without a workspace argument, for callers that cannot allocate device
  * memory: code under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation.  Arguments, outputs, layout and errors are those of ts_chain_marginals without
- * ws / ws_bytes; the kernels and the results are the same.  The call allocates nothing: its
+ * ws / ws_bytes.  The call allocates nothing: its
  * scratch is one array of ts_chain_noalloc_scratch_bytes() bytes (64 MiB) per GPU inside the
  * library, held from the first call on that GPU until the process ends.  Every problem whose
  * ts_chain_workspace_bytes(TS_OP_MARGINALS, B, N, C) does not exceed it is accepted (the
- * single-launch path for small label sets needs no scratch).  Beyond that, a problem that fits
- * without the vector recursions' buffers (some with fewer than 32 labels) is computed without
- * them, and any other returns TS_ERR_BAD_DIM before any device call.
+ * single-launch path for small label sets needs no scratch), with that call's kernels and results.
+ * Beyond that, a problem that fits without the vector recursions' buffers (some with fewer than 32
+ * labels, whose workspace these make two to eight times as large) is computed by the kernels behind
+ * them, with results that differ from ts_chain_marginals' by rounding; any other returns
+ * TS_ERR_BAD_DIM before any device call.
  * Every call on one GPU shares that GPU's array, which keeps the last call's contents (the
  * kernels need none of it cleared): calls that overlap on one GPU, from different streams
  * or threads, race on it and must be serialised by the caller.  TS_CHECK=1 copies the

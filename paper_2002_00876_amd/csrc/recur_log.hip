@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(64) void k_rec_meet(RecLogArgs a) {
 // known to some 1e-7, an error of about 1e-8 per chunk (row-normalised, C = 8, N = 65536: 1.4e-4
 // before this, see the tests).  Rare, so simple: four threads share a column.
 __global__ __launch_bounds__(1024) void k_rec_refine(RecLogArgs a) {
-    __shared__ double vec[kMaxLabels], part[4][kMaxLabels], red[2];
+    __shared__ double vec[kMaxLabels], part[4][kMaxLabels];
     __shared__ bool done;
     const int k = (int)(blockIdx.x / (unsigned)a.B), b = (int)(blockIdx.x - k * (unsigned)a.B);
     if (!a.fine[b]) return;

@@ -61,7 +61,7 @@ def test_large_masks(C, N, mask):
 
 
 @pytest.mark.parametrize("mask", MASKS[1:])
-@pytest.mark.parametrize("C,N", [(24, 900), (75, 400), (128, 600), (256, 300)])
+@pytest.mark.parametrize("C,N", [(24, 900), (75, 400), (128, 600), (129, 1000), (256, 300)])
 def test_masks_on_every_path(C, N, mask):
     # one edge (in a middle chunk, in the last) masked whole: past it float64 holds the scores to
     # the mask's last bit only, and decisions are those of sums from the sequence's start
@@ -195,6 +195,27 @@ def test_row_normalised_potentials(B, N, C):
     if N * C * C <= 1 << 24:
         z2, _ = binding.marginals(tp, tl)
         check_logz(z2.cpu().numpy(), ref, "logZ (marginals call)")
+
+
+def test_refined_log_z_replays_in_a_graph():
+    # the last chunk to end adds the others up: every replay counts them anew
+    p = torch.from_numpy(_normalised(39700, 2, 4000, 8)).cuda()
+    lens = torch.tensor([4000, 3100], device="cuda", dtype=torch.int32)
+    z = torch.empty(2, device="cuda")
+    ws = torch.empty(binding.workspace_bytes(binding.OP_LOGPARTITION, 2, 4000, 8), device="cuda",
+                     dtype=torch.uint8)
+    want = binding.logpartition(p, lens, out=z, ws=ws).clone()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        binding.logpartition(p, lens, out=z, ws=ws)
+    torch.cuda.synchronize()
+    for _ in range(4):
+        z.fill_(-7)
+        binding.viterbi(p, lens)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(z, want)
 
 
 def test_chunk_scales_have_no_bias():
